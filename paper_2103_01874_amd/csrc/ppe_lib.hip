@@ -144,10 +144,11 @@ size_t spec_elem_bytes(const ppe_desc_t* d) {
 
 // Tile of a marching stencil kernel run by `nt` threads per block: TXT = nx
 // when nx <= max_txt, else the largest divisor of nx up to max_txt; TJ rows so
-// that a tile plane has about `points` interior cells; KC planes per chunk so
-// that an instance gets about 2048 blocks.
+// that a tile plane has about `points` interior cells and its halo ring at most
+// `ring` points; KC planes per chunk, at most max_planes.
 bool march_shape(const ppe_desc_t& d, int points, int max_txt, const char* env, ppe_plan_s::MarchCfg& c,
-                 int nt = kMarchThreads, int max_planes = 16) {
+                 int nt = kMarchThreads, int max_planes = 16, int ring = kRingPT * kMarchThreads, int blocks = 2048,
+                 bool xcd_bands = true) {
   March& M = c.m;
   c.nt = nt;
   if (tune_env("PPE_TUNE_TXT") > 0) max_txt = tune_env("PPE_TUNE_TXT");
@@ -162,23 +163,46 @@ bool march_shape(const ppe_desc_t& d, int points, int max_txt, const char* env, 
   }
   M.tj = std::max(1, std::min(points / M.txt, d.ny));
   if (tune_env(env) > 0) M.tj = std::max(1, std::min(tune_env(env), d.ny));
-  while (M.tj > 1 && 2 * M.txt + 2 * M.tj > kRingPT * nt) --M.tj;
+  while (M.tj > 1 && 2 * M.txt + 2 * M.tj > ring) --M.tj;
   if ((long long)M.tj * M.txt > (long long)nt * kMaxPPT) return false;
   M.ntx = d.nx / M.txt;
   M.ntj = (d.ny + M.tj - 1) / M.tj;
-  const int target = tune_env("PPE_TUNE_MARCH_BLOCKS") > 0 ? tune_env("PPE_TUNE_MARCH_BLOCKS") : 2048;
-  int nkc = std::max(1, (target + M.ntx * M.ntj - 1) / (M.ntx * M.ntj));
-  // and at most 16 planes per block: with fewer, longer marches the final
-  // set of resident blocks leaves the GPU idle for longer (512x256x512:
-  // 128 planes per block, k_correct 1387 us; 16 planes, 1306 us)
+  // Chunks of planes.  The residual passes: about `blocks` blocks an instance.
+  // k_rhs and k_correct (blocks = 0): a block pays about 0.7 of a plane for the
+  // planes at its ends, and a grid of a few blocks per CU should load the CUs
+  // evenly, with at least two on each for their loads to overlap (64x64x64 x 8
+  // k_correct 48 -> 40 us, 128x512x96 121 -> 111 against 2048 blocks an instance).
+  const int ntile = M.ntx * M.ntj;
   if (tune_env("PPE_TUNE_MAX_PLANES") > 0) max_planes = tune_env("PPE_TUNE_MAX_PLANES");
-  nkc = std::max(nkc, (d.nz + max_planes - 1) / max_planes);
-  nkc = std::min(nkc, std::max(1, d.nz / 2));
-  M.kc = (d.nz + nkc - 1) / nkc;
+  int nkc = (d.nz + max_planes - 1) / max_planes;
+  if (blocks > 0) {
+    nkc = std::min(std::max(nkc, (blocks + ntile - 1) / ntile), std::max(1, d.nz / 2));
+    M.kc = (d.nz + nkc - 1) / nkc;
+  } else {
+    M.kc = d.nz;
+    double best = 0.0;
+    for (; nkc <= std::max(1, d.nz / 2); ++nkc) {
+      const int kc = (d.nz + nkc - 1) / nkc;
+      const double per_cu = (double)ntile * d.batch * ((d.nz + kc - 1) / kc) / 256.0;
+      const double score = per_cu / std::ceil(per_cu) * std::min(1.0, per_cu / 2.0) * kc / (kc + 0.7);
+      if (score > best * 1.001) {
+        best = score;
+        M.kc = kc;
+      }
+    }
+  }
   M.nkc = (d.nz + M.kc - 1) / M.kc;
   M.nt = M.ntx * M.ntj * M.nkc;
-  M.per_xcd = (M.nt + 7) / 8;
-  c.grid = 8 * M.per_xcd;
+  // Runs of a sixteenth of a plane's tiles: the XCDs march the same planes, each
+  // in two bands of tile rows.  With one contiguous range each they march
+  // planes a power of two apart, whose lines share channels whatever the
+  // arrays' alignment (512x256x512: k_rhs 880 -> 818 us, k_correct 1170-1310,
+  // by where the arrays lie, -> 1126; 384x192x324: 331 -> 323 and 459 -> 443).
+  // Planes of few tiles keep the ranges: bands of one or two tile rows re-read
+  // more halo rows than they hold (96x64x96 x 12, 26 tiles: 95 -> 105 us).
+  const int bands = tune_env("PPE_TUNE_BANDS") > 0 ? tune_env("PPE_TUNE_BANDS") : (xcd_bands && ntile >= 64 ? 16 : 1);
+  M.run = bands > 1 ? std::max(1, ntile / bands) : (M.nt + 7) / 8;
+  c.grid = 8 * M.run * (((M.nt + M.run - 1) / M.run + 7) / 8);
   const int npt = M.txt * M.tj;
   c.ppt = 1;
   while (c.ppt * nt < npt) c.ppt *= 2;
@@ -285,35 +309,38 @@ bool shape_plan(ppe_plan_s* p, size_t lds_limit = 65536) {
   if (p->src_vec != 1) p->src_vec = 2;
   // z-marching stencils: TXT x TJ tiles (TXT a divisor of nx, <= 128), KC planes
   // per chunk; the tile height per kernel trades halo traffic against registers
-  // On large planes the two big stencils take 64x8 tiles, which fetch fewer
-  // halo rows per interior row than 64x4 where those rows no longer stay in
-  // L2: k_rhs with 512 threads, one point each (planes of >= 16 K cells);
-  // k_correct with 256 threads, two points each (held to four waves per SIMD
-  // by its launch bounds), marching up to 32 planes per block (planes of
-  // >= 64 K cells).  512x256x512 FP64: k_rhs 947 -> 921 us, k_correct
-  // 1284 -> 1241 us, step 3.23 -> 3.14 ms.  The residual passes take 64x8
-  // tiles (two points per thread) on the same planes: k_resid of the
-  // FP32-spectrum path 304 -> 273 us at 512x256x512 (at 256x128 planes
-  // k_resid_var ran 60 -> 70 us that way).  On smaller planes the halo rows
-  // hit L2 and the 64x4 tiles keep more waves in flight.
+  // k_rhs and k_correct take one point per thread.  512 threads (64 x 8 tiles)
+  // fetch fewer halo rows per interior row than 256 (64 x 4) and win where
+  // those rows no longer stay in L2: k_correct from planes of 64 K cells
+  // (512x256x512: 1107 against 1184 us, 512x128x256: 327 against 345;
+  // 384x192x324: 470 against 463), k_rhs from 16 K cells where the tile rows
+  // are whole wavefronts (256x256x256: 213 against 224; rows of 48 cells leave
+  // threads idle, 96x64x96 x 12: 99 against 88).  A block marches at most 16
+  // planes; 32 on planes of 128 K cells, and in k_correct's small tiles (a
+  // 256x128x256 step 401.6 against 403.5 us: the k_rhs that follows is faster).  The
+  // residual passes take 64 x 8 tiles, two points per thread, on the planes of
+  // k_correct's (k_resid_var) or on all (k_resid).
   const auto nt_of = [](const char* env, int def) {
     const int v = tune_env(env);
-    return (v == 256 || v == 512 || v == 1024) ? v : def;
+    return (v == 256 || v == 512) ? v : def;
   };
   const long long plane_cells = (long long)d.nx * d.ny;
-  const bool big_rhs = plane_cells >= 16384, big_cor = plane_cells >= 65536;
-  const int nt_rhs = nt_of("PPE_TUNE_NT_RHS", big_rhs ? 512 : kMarchThreads);
-  const int nt_cor = nt_of("PPE_TUNE_NT_COR", kMarchThreads);
+  const bool big_cor = plane_cells >= 65536;
+  const bool big_rhs = big_cor || (plane_cells >= 16384 && d.nx % 64 == 0);
+  const int nt_rhs = nt_of("PPE_TUNE_NT_RHS", big_rhs ? 512 : 256);
+  const int nt_cor = nt_of("PPE_TUNE_NT_COR", big_cor ? 512 : 256);
+  const int planes = plane_cells >= 131072 ? 32 : 16;
   const int planes_cor =
-      tune_env("PPE_TUNE_MAX_PLANES_COR") > 0 ? tune_env("PPE_TUNE_MAX_PLANES_COR") : (big_cor ? 32 : 16);
-  if (!march_shape(d, big_rhs ? 512 : 256, 64, "PPE_TUNE_TJ_RHS", p->mrhs, nt_rhs) ||
-      !march_shape(d, big_cor ? 512 : 256, 64, "PPE_TUNE_TJ_COR", p->mcor, nt_cor, planes_cor) ||
+      tune_env("PPE_TUNE_MAX_PLANES_COR") > 0 ? tune_env("PPE_TUNE_MAX_PLANES_COR") : (big_cor ? planes : 32);
+  if (!march_shape(d, nt_rhs, 64, "PPE_TUNE_TJ_RHS", p->mrhs, nt_rhs, planes, nt_rhs, 0) ||
+      !march_shape(d, nt_cor, 64, "PPE_TUNE_TJ_COR", p->mcor, nt_cor, planes_cor, nt_cor, 0) ||
       !march_shape(d, big_cor ? 512 : 256, 64, "PPE_TUNE_TJ_RES", p->mres) ||
       // the refinement residual: 64 x 8 tiles at every plane size (against
       // 64 x 4 below 64 K cells: 7-17% faster from 64^3 to 256 x 128 x 256)
-      !march_shape(d, 512, 64, "PPE_TUNE_TJ_RS", p->mrs))
+      // (one range per XCD: 512x256x512 258 against 263 us)
+      !march_shape(d, 512, 64, "PPE_TUNE_TJ_RS", p->mrs, kMarchThreads, 16, kRingPT * kMarchThreads, 2048, false))
     return false;
-  if ((size_t)3 * p->mcor.tslots * 8 > 65536) return false;
+  if (p->mrhs.ppt != 1 || p->mcor.ppt != 1 || (size_t)6 * p->mcor.tslots * 8 > 65536) return false;
   // per-instance partial-sum stride: the largest grid.x of a reducing kernel
   const long long nrows = (long long)d.ny * d.nz;
   const long long xgrid = (nrows + 1) / 2;  // bound on the row-pair grids, whatever the launch shape
@@ -466,17 +493,13 @@ Work<TS> make_work(ppe_plan_s* p, int inst0) {
     default: return PPE_ERR_UNSUPPORTED;            \
   }
 
-// Launch CALL with PPT and NT the marching kernel's points per thread and
-// threads per block of launch shape CFG.
-#define PPE_MARCH_SWITCH(CFG, CALL)                                                  \
-  switch ((CFG).nt * 8 + (CFG).ppt) {                                               \
-    case 256 * 8 + 1: { constexpr int PPT = 1, NT = 256; CALL; } break;            \
-    case 256 * 8 + 2: { constexpr int PPT = 2, NT = 256; CALL; } break;            \
-    case 256 * 8 + 4: { constexpr int PPT = 4, NT = 256; CALL; } break;            \
-    case 512 * 8 + 1: { constexpr int PPT = 1, NT = 512; CALL; } break;            \
-    case 512 * 8 + 2: { constexpr int PPT = 2, NT = 512; CALL; } break;            \
-    case 1024 * 8 + 1: { constexpr int PPT = 1, NT = 1024; CALL; } break;          \
-    default: return PPE_ERR_UNSUPPORTED;                                            \
+// Launch CALL with NT the threads per block of launch shape CFG (k_rhs and
+// k_correct: one point per thread).
+#define PPE_MARCH_SWITCH(CFG, CALL)                     \
+  switch ((CFG).nt) {                                   \
+    case 256: { constexpr int NT = 256; CALL; } break;  \
+    case 512: { constexpr int NT = 512; CALL; } break;  \
+    default: return PPE_ERR_UNSUPPORTED;                \
   }
 
 #define PPE_E_SWITCH(EVAL, CALL)  \
@@ -667,7 +690,7 @@ ppe_status_t solve_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb) 
   dim3 xgrid((unsigned)((npairs + p->rp - 1) / p->rp), 1, nb);
   dim3 xblock(p->rp * p->fx.tc);
   PPE_TIMED(p, "k_rhs",
-            PPE_MARCH_SWITCH(p->mrhs, (k_rhs<TS, PPT, true, NT><<<dim3(p->mrhs.grid, 1, nb), NT, march_lds(p->mrhs, 2),
+            PPE_MARCH_SWITCH(p->mrhs, (k_rhs<TS, true, NT><<<dim3(p->mrhs.grid, 1, nb), NT, march_lds(p->mrhs, 4),
                                                               p->stream>>>(tab, g, p->mrhs.m, W))));
   // the right-hand-side sums are reduced by block 0 of the first row FFT
   PPE_TIMED(p, "k_r2c",
@@ -716,8 +739,8 @@ ppe_status_t varcoef_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb
   dim3 xgrid((unsigned)((npairs + p->rp - 1) / p->rp), 1, nb);
   dim3 xblock(p->rp * p->fx.tc);
   PPE_TIMED(p, "k_rhs",
-            PPE_MARCH_SWITCH(p->mrhs, (k_rhs<TS, PPT, false, NT><<<dim3(p->mrhs.grid, 1, nb), NT,
-                                                               march_lds(p->mrhs, 1), p->stream>>>(tab, g,
+            PPE_MARCH_SWITCH(p->mrhs, (k_rhs<TS, false, NT><<<dim3(p->mrhs.grid, 1, nb), NT,
+                                                               march_lds(p->mrhs, 0), p->stream>>>(tab, g,
                                                                                                    p->mrhs.m, W))));
   finish(p, tab, inst0, nb, p->mrhs.grid, FIN_RHS, 0, tol);
   const int hs = max_iters + 1;
@@ -780,8 +803,8 @@ template <typename TS>
 ppe_status_t defect_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb, double* out) {
   Work<TS> W = make_work<TS>(p, inst0);
   PPE_TIMED(p, "k_rhs",
-            PPE_MARCH_SWITCH(p->mrhs, (k_rhs<TS, PPT, false, NT><<<dim3(p->mrhs.grid, 1, nb), NT,
-                                                               march_lds(p->mrhs, 1), p->stream>>>(tab, p->g,
+            PPE_MARCH_SWITCH(p->mrhs, (k_rhs<TS, false, NT><<<dim3(p->mrhs.grid, 1, nb), NT,
+                                                               march_lds(p->mrhs, 0), p->stream>>>(tab, p->g,
                                                                                                    p->mrhs.m, W))));
   PPE_TIMED(p, "k_resid_var",
             PPE_PPT_SWITCH(p->mres.ppt, (k_resid_var<TS, PPT, 2><<<dim3(p->mres.grid, 1, nb), kMarchThreads,
@@ -1083,8 +1106,8 @@ ppe_status_t ppe_rhs(ppe_plan_t p, const double* rho0, const double* dt, const d
     rho_min_pass(p, tab, i0, nb);
     Work<double> W = make_work<double>(p, i0);
     PPE_TIMED(p, "k_rhs",
-              PPE_MARCH_SWITCH(p->mrhs, (k_rhs<double, PPT, true, NT><<<dim3(p->mrhs.grid, 1, nb), NT,
-                                                                    march_lds(p->mrhs, 2), p->stream>>>(
+              PPE_MARCH_SWITCH(p->mrhs, (k_rhs<double, true, NT><<<dim3(p->mrhs.grid, 1, nb), NT,
+                                                                    march_lds(p->mrhs, 4), p->stream>>>(
                                                tab, g, p->mrhs.m, W))));
     finish(p, tab, i0, nb, p->mrhs.grid, FIN_RHS, 0);
     for (int i = 0; i < nb; ++i)
@@ -1202,8 +1225,8 @@ ppe_status_t ppe_correct(ppe_plan_t p, const double* rho0, const double* dt, con
       q.dt = dt[i0 + i];
     }
     PPE_TIMED(p, "k_correct",
-              PPE_MARCH_SWITCH(p->mcor, (k_correct<PPT, NT><<<dim3(p->mcor.grid, 1, nb), NT,
-                                                            march_lds(p->mcor, 3), p->stream>>>(
+              PPE_MARCH_SWITCH(p->mcor, (k_correct<NT><<<dim3(p->mcor.grid, 1, nb), NT,
+                                                            march_lds(p->mcor, 6), p->stream>>>(
                                                tab, g, p->mcor.m, p->partial, p->pstride, i0))));
     finish(p, tab, i0, nb, p->mcor.grid, FIN_CORRECT, 0, tol);
   }
