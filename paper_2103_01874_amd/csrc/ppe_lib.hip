@@ -692,10 +692,10 @@ ppe_status_t solve_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb) 
   PPE_TIMED(p, "k_rhs",
             PPE_MARCH_SWITCH(p->mrhs, (k_rhs<TS, true, NT><<<dim3(p->mrhs.grid, 1, nb), NT, march_lds(p->mrhs, 4),
                                                               p->stream>>>(tab, g, p->mrhs.m, W))));
-  // the right-hand-side sums are reduced by block 0 of the first row FFT
+  // (the sums of the kernel before a forward row transform are reduced by its block 0)
   PPE_TIMED(p, "k_r2c",
-            PPE_FFT_SWITCH(p->fx_ct, p->fx, fx, (k_r2c<TS, E><<<xgrid, xblock, p->lds_x, p->stream>>>(
-                                   tab, g, fx, W, p->b64, p->rp, 0, FinishArgs{p->mrhs.grid, tol}))));
+            PPE_FFT_SWITCH(p->fx_ct, p->fx, fx, (k_r2c<TS, E><<<dim3(xgrid.x + 1, 1, nb), xblock, p->lds_x, p->stream>>>(
+                                   tab, g, fx, W, p->b64, p->rp, 0, FinishArgs{p->mrhs.grid, FIN_RHS, tol, nullptr, 0}))));
   ppe_status_t st = launch_chain<TS>(p, W, nb, 0);
   if (st != PPE_OK) return st;
   PPE_TIMED(p, "k_c2r",
@@ -710,10 +710,9 @@ ppe_status_t solve_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb) 
                 PPE_PPT_SWITCH(p->mrs.ppt, (k_resid<TS, PPT><<<dim3(p->mrs.grid, 1, nb), kMarchThreads,
                                                                march_lds(p->mrs, 1), p->stream>>>(
                                                 tab, g, p->mrs.m, W, rs))));
-      finish(p, tab, inst0, nb, p->mrs.grid, FIN_RESID, 1);
       PPE_TIMED(p, "k_r2c",
-                PPE_FFT_SWITCH(p->fx_ct, p->fx, fx, (k_r2c<TS, E><<<xgrid, xblock, p->lds_x, p->stream>>>(
-                                       tab, g, fx, W, static_cast<const TS*>(rs), p->rp, 1, FinishArgs{0, 0.0}))));
+                PPE_FFT_SWITCH(p->fx_ct, p->fx, fx, (k_r2c<TS, E><<<dim3(xgrid.x + 1, 1, nb), xblock, p->lds_x, p->stream>>>(
+                                       tab, g, fx, W, static_cast<const TS*>(rs), p->rp, 1, FinishArgs{p->mrs.grid, FIN_RESID, 0.0, nullptr, 0}))));
       st = launch_chain<TS>(p, W, nb, 1);
       if (st != PPE_OK) return st;
       PPE_TIMED(p, "k_c2r",
@@ -780,12 +779,14 @@ ppe_status_t varcoef_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb
                 PPE_PPT_SWITCH(p->mres.ppt, (k_resid_var<TS, PPT, 0><<<dim3(p->mres.grid, 1, nb), kMarchThreads,
                                                                           march_lds(p->mres, 2), p->stream>>>(
                                                 tab, g, p->mres.m, W, p->r64, 1))));
-    finish(p, tab, inst0, nb, p->mres.grid, it == max_iters ? FIN_RESID_LAST : FIN_RESID, 1, 0.0,
-           h0 ? h0 + it : nullptr, hs);
-    if (it == max_iters) break;
+    double* const h = h0 ? h0 + it : nullptr;
+    if (it == max_iters) {
+      finish(p, tab, inst0, nb, p->mres.grid, FIN_RESID_LAST, 1, 0.0, h, hs);
+      break;
+    }
     PPE_TIMED(p, "k_r2c",
-              PPE_FFT_SWITCH(p->fx_ct, p->fx, fx, (k_r2c<TS, E><<<xgrid, xblock, p->lds_x, p->stream>>>(
-                                     tab, g, fx, W, p->r64, p->rp, 1, FinishArgs{0, 0.0}))));
+              PPE_FFT_SWITCH(p->fx_ct, p->fx, fx, (k_r2c<TS, E><<<dim3(xgrid.x + 1, 1, nb), xblock, p->lds_x, p->stream>>>(
+                                     tab, g, fx, W, p->r64, p->rp, 1, FinishArgs{p->mres.grid, FIN_RESID, 0.0, h, hs}))));
     ppe_status_t st = launch_chain<TS>(p, W, nb, 1);
     if (st != PPE_OK) return st;
     PPE_TIMED(p, "k_c2r",
@@ -1007,6 +1008,8 @@ ppe_status_t ppe_plan(const ppe_desc_t* desc, void* stream, ppe_plan_t* out) {
     }
   }
   std::vector<double> twx = twiddles(d.nx), twz = twiddles(d.nz);
+  const std::vector<double> scal0(B * kNScal, 0.0);
+  ok &= hipMemcpy(p->scal, scal0.data(), scal0.size() * 8, hipMemcpyHostToDevice) == hipSuccess;
   ok &= hipMemcpy(p->lamx, lx.data(), lx.size() * 8, hipMemcpyHostToDevice) == hipSuccess;
   ok &= hipMemcpy(p->lamz, lz.data(), lz.size() * 8, hipMemcpyHostToDevice) == hipSuccess;
   ok &= hipMemcpy(p->fx.tw, twx.data(), twx.size() * 8, hipMemcpyHostToDevice) == hipSuccess;
@@ -1227,8 +1230,7 @@ ppe_status_t ppe_correct(ppe_plan_t p, const double* rho0, const double* dt, con
     PPE_TIMED(p, "k_correct",
               PPE_MARCH_SWITCH(p->mcor, (k_correct<NT><<<dim3(p->mcor.grid, 1, nb), NT,
                                                             march_lds(p->mcor, 6), p->stream>>>(
-                                               tab, g, p->mcor.m, p->partial, p->pstride, i0))));
-    finish(p, tab, i0, nb, p->mcor.grid, FIN_CORRECT, 0, tol);
+                                               tab, g, p->mcor.m, p->partial, p->pstride, i0, p->scal, tol))));
   }
   return hipGetLastError() == hipSuccess ? PPE_OK : PPE_ERR_DEVICE;
 }

@@ -68,3 +68,24 @@ def test_march_without_the_split_term(shape, ybc):
     (p,), _, _, _ = gpu_varcoef([pr], 2, 0.0)
     _, ref = oracle_fp(pr, 2)
     assert PU.rel(p, ref["p"]) <= 1e-12
+
+
+@pytest.mark.parametrize("precision", [binding.PPE_PREC_FP64, binding.PPE_PREC_MIXED])
+def test_statistics_of_a_batch_equal_single_runs(precision):
+    """The sums reduced inside other launches (block 0 of the row transform,
+    the last block of the projection): instances that converge after different
+    sweeps, twice in a row, give the fields they give alone, bit for bit, and
+    the statistics to the rounding of their sums (the blocks of a pass depend
+    on the batch; a residual of 1e-7 leaves 1e-9 of it)."""
+    prs = [synth.sheet_problem(32, 16, 24, seed=9700 + r, rho_l=100.0 * r) for r in (1, 3, 10)]
+    alone = [gpu_varcoef([pr], 40, 1e-7, precision=precision, correct=True) for pr in prs]
+    close = lambda a, b: abs(a - b) <= 1e-9 * abs(b)
+    for _ in range(2):
+        p, recs, hist, outs = gpu_varcoef(prs, 40, 1e-7, precision=precision, correct=True)
+        for i, (p1, r1, h1, o1) in enumerate(alone):
+            assert np.array_equal(p[i], p1[0])
+            assert all(np.array_equal(outs[i][k], o1[0][k]) for k in ("u", "v", "w"))
+            assert recs[i]["iters"] == r1[0]["iters"] and recs[i]["status"] == r1[0]["status"]
+            assert np.allclose(hist[i], h1[0], rtol=1e-9, atol=0.0)
+            assert all(close(outs[i]["info"][k], o1[0]["info"][k]) for k in ("res_rel", "div_l2", "div_max", "div0_l2"))
+    assert len({r["iters"] for r in recs}) > 1
