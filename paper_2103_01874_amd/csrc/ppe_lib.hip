@@ -1450,6 +1450,35 @@ ppe_status_t ppe_ring_destroy(ppe_ring_t r) {
   return PPE_OK;
 }
 
+namespace {
+// Tiles and planes per block of k_predict_fused: one block runs on a CU at a
+// time, and pays about two planes for the ends of its march.
+PredFuse predict_shape(const Geom& g, int nb) {
+  PredFuse m;
+  m.ntx = (g.nx + 63) / 64;
+  m.w = (g.nx + m.ntx - 1) / m.ntx;
+  m.ntx = (g.nx + m.w - 1) / m.w;
+  m.ntj = (g.ny + kFuseTJ - 1) / kFuseTJ;
+  const int T = m.ntx * m.ntj;
+  m.kc = g.nz;
+  double best = 0.0;
+  for (int nkc = 1; nkc <= g.nz; ++nkc) {
+    const int kc = (g.nz + nkc - 1) / nkc;
+    const double rounds = (double)T * nb * ((g.nz + kc - 1) / kc) / 256.0;
+    const double score = rounds / std::ceil(rounds) * kc / (kc + 2.0);
+    if (score > best * 1.001) {
+      best = score;
+      m.kc = kc;
+    }
+  }
+  if (tune_env("PPE_TUNE_PREDICT_RUN") > 0) m.kc = std::min(g.nz, tune_env("PPE_TUNE_PREDICT_RUN"));
+  m.nkc = (g.nz + m.kc - 1) / m.kc;
+  m.nt = T * m.nkc;
+  m.run = std::max(1, T / 8);  // an XCD takes a band of tile rows of every chunk
+  return m;
+}
+}  // namespace
+
 ppe_status_t ppe_predict(ppe_plan_t p, const ppe_predict_t* in, double* const* up, double* const* vp,
                          double* const* wp) {
   if (!p || !in || !up || !vp || !wp) return PPE_ERR_ARG;
@@ -1502,50 +1531,16 @@ ppe_status_t ppe_predict(ppe_plan_t p, const ppe_predict_t* in, double* const* u
       const PredPtrs& t = tab.in[i];
       alias = alias && t.uv == t.u && t.vv == t.v && t.wv == t.w;
     }
-    if (tiled && alias && tune_env("PPE_TUNE_PREDICT_NO_MARCH") == 0) {
-      const auto run_of = [](const char* env, int def) {
-        const int v = tune_env(env) > 0 ? tune_env(env) : tune_env("PPE_TUNE_PREDICT_RUN");
-        return v > 0 ? v : def;
-      };
-      // slabs per block: at 256x128x256 the y marches (u, w) ran fastest with
-      // 12 (u/w 281/247 us at 16, 270/239 at 12, 275-287/244-257 at 8-14), the
-      // z march (v) with 16 or 32 (293; 315-351 at 20-24)
-      const int run_u = run_of("PPE_TUNE_PREDICT_RUN_U", 12), run_v = run_of("PPE_TUNE_PREDICT_RUN_V", 16),
-                run_w = run_of("PPE_TUNE_PREDICT_RUN_W", 12);
-      const unsigned ntx = (unsigned)(g.nx / kPredTX);
-      const unsigned ty = ntx * (unsigned)((g.ny + kPredTR - 1) / kPredTR);
-      const unsigned tz = ntx * (unsigned)((g.nz + kPredTR - 1) / kPredTR);
-      const auto gy = [&](int run) { return dim3(ty * (unsigned)((g.nz + run - 1) / run), 1, nb); };
-      const auto gz = [&](int run) { return dim3(tz * (unsigned)((g.ny + run - 1) / run), 1, nb); };
-      constexpr int nt = kPredTX * kPredTR;
-      if (tune_env("PPE_TUNE_PREDICT_U_PLANES") == 0 && tune_env("PPE_TUNE_PREDICT_SEPARATE") == 0) {
-        // the three components in one launch (u and w through y rows, v
-        // through z planes), each block range starting on a multiple of 8
-        const unsigned nu = gz(run_u).x, nv = gy(run_v).x, nw = gz(run_w).x;
-        const unsigned nblk = ((nu + 7u) & ~7u) + ((nv + 7u) & ~7u) + nw;
-        PPE_TIMED(p, "k_predict", {
-          k_predict_march_uvw<<<dim3(nblk, 1, nb), nt, 0, p->stream>>>(tab, g, run_u, run_v, run_w, nu, nv, nw);
-          if (g.ybc == 1) {  // the outflow top face of v
-            const unsigned tblocks = (unsigned)(((long long)g.nx * g.nz + 255) / 256);
-            k_predict_vtop<<<dim3(tblocks, 1, nb), 256, 0, p->stream>>>(tab, g);
-          }
-        });
-        continue;
-      }
-      // u marches through y rows like w (faster than through z planes)
-      if (tune_env("PPE_TUNE_PREDICT_U_PLANES") != 0) {
-        PPE_TIMED(p, "k_predict_u", (k_predict_march<0><<<gy(run_u), nt, 0, p->stream>>>(tab, g, run_u)));
-      } else {
-        PPE_TIMED(p, "k_predict_u", (k_predict_march<3><<<gz(run_u), nt, 0, p->stream>>>(tab, g, run_u)));
-      }
-      PPE_TIMED(p, "k_predict_v", {
-        k_predict_march<1><<<gy(run_v), nt, 0, p->stream>>>(tab, g, run_v);
-        if (g.ybc == 1) {  // the outflow top face
+    if (alias && tune_env("PPE_TUNE_PREDICT_GLOBAL") == 0) {
+      const PredFuse m = predict_shape(g, nb);
+      const unsigned grid = 8u * m.run * ((((unsigned)m.nt + m.run - 1) / m.run + 7u) / 8u);
+      PPE_TIMED(p, "k_predict", {
+        k_predict_fused<<<dim3(grid, 1, nb), 64 * kFuseTJ, 0, p->stream>>>(tab, g, m);
+        if (g.ybc == 1) {  // the outflow top face of v
           const unsigned tblocks = (unsigned)(((long long)g.nx * g.nz + 255) / 256);
           k_predict_vtop<<<dim3(tblocks, 1, nb), 256, 0, p->stream>>>(tab, g);
         }
       });
-      PPE_TIMED(p, "k_predict_w", (k_predict_march<2><<<gz(run_w), nt, 0, p->stream>>>(tab, g, run_w)));
       continue;
     }
     if (tiled) {
@@ -1554,20 +1549,17 @@ ppe_status_t ppe_predict(ppe_plan_t p, const ppe_predict_t* in, double* const* u
       const dim3 gz(ntx * (unsigned)((g.nz + kPredTR - 1) / kPredTR), (unsigned)g.ny, nb);
       constexpr int nt = kPredTX * kPredTR;
       PPE_TIMED(p, "k_predict_u", {
-        if (alias) k_predict_tile<0, true><<<gy, nt, 0, p->stream>>>(tab, g);
-        else k_predict_tile<0, false><<<gy, nt, 0, p->stream>>>(tab, g);
+        k_predict_tile<0><<<gy, nt, 0, p->stream>>>(tab, g);
       });
       PPE_TIMED(p, "k_predict_v", {
-        if (alias) k_predict_tile<1, true><<<gy, nt, 0, p->stream>>>(tab, g);
-        else k_predict_tile<1, false><<<gy, nt, 0, p->stream>>>(tab, g);
+        k_predict_tile<1><<<gy, nt, 0, p->stream>>>(tab, g);
         if (g.ybc == 1) {  // the outflow top face
           const unsigned tblocks = (unsigned)(((long long)g.nx * g.nz + 255) / 256);
           k_predict_vtop<<<dim3(tblocks, 1, nb), 256, 0, p->stream>>>(tab, g);
         }
       });
       PPE_TIMED(p, "k_predict_w", {
-        if (alias) k_predict_tile<2, true><<<gz, nt, 0, p->stream>>>(tab, g);
-        else k_predict_tile<2, false><<<gz, nt, 0, p->stream>>>(tab, g);
+        k_predict_tile<2><<<gz, nt, 0, p->stream>>>(tab, g);
       });
       continue;
     }

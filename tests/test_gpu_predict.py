@@ -250,3 +250,32 @@ def test_one_launch_equals_launch_per_component(shape, ybc, monkeypatch):
         check(g, r, a3, f"one launch {shape} ybc={ybc}")
         for a, b in zip(a3, b3):
             assert np.array_equal(a, b)
+
+
+FUSED = [(1, 4, 1), (2, 5, 2), (16, 8, 3), (54, 9, 6), (64, 16, 1), (72, 7, 12), (96, 17, 4), (162, 8, 6), (192, 33, 2)]
+
+
+@pytest.mark.parametrize("ybc", [0, 1])
+@pytest.mark.parametrize("shape", FUSED)
+def test_one_march_for_the_three_components(shape, ybc, monkeypatch):
+    """The march that forms every flux once, on tiles of any width (one
+    column, one row of tiles, a narrower last tile, periodic halos that wrap
+    more than once), partial tile rows and chunks of 1, 2 and all planes, with
+    the face forces on every other shape; against the oracle and, to the same
+    rounding as the tiles, the one-thread-per-face kernels."""
+    g = O.Grid(*shape, 1.1, 0.8, 1.3, ybc=ybc)
+    r = random_inputs(g, 900 + sum(shape) + ybc)
+    if sum(shape) % 2 == 0:
+        rng = np.random.default_rng(sum(shape))
+        r["fsx"], r["fsz"] = rng.standard_normal(g.shape), rng.standard_normal(g.shape)
+        r["fsy"] = rng.standard_normal(g.vshape)
+    monkeypatch.setenv("PPE_TUNE_PREDICT_GLOBAL", "1")
+    (per_face,) = gpu_predict(g, [r])
+    monkeypatch.delenv("PPE_TUNE_PREDICT_GLOBAL")
+    for run in ("0", "1", "2", str(shape[2])):
+        monkeypatch.setenv("PPE_TUNE_PREDICT_RUN", run)
+        (fused,) = gpu_predict(g, [r])
+        check(g, r, fused, f"fused {shape} ybc={ybc} run={run}")
+        for name, a, b in zip("uvw", fused, per_face):
+            d = np.abs(a - b).max()
+            assert d <= 4 * np.finfo(np.float64).eps * np.abs(b).max(), (name, d)
