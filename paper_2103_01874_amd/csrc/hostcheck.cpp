@@ -215,7 +215,6 @@ int hc_fft_ct(int n, int dir, const double* in, double* out) {
     default:
       return -1;
   }
-#undef HC_CT
   for (int i = 0; i < n; ++i) {
     out[2 * i] = buf[lslot<true>(i, 1)].re;
     out[2 * i + 1] = buf[lslot<true>(i, 1)].im;
@@ -224,6 +223,40 @@ int hc_fft_ct(int n, int dir, const double* in, double* out) {
 }
 
 // 0 if the compile-time plan of n equals the host factorisation.
+// The transform of a length of kMixedPlans through its compile-time plan.
+int hc_fft_mixed(int n, int dir, const double* in, double* out) {
+  std::vector<double> tw = twiddles(n);
+  std::vector<cplx<double>> buf(padded_len(n)), regs((size_t)n);
+  for (int i = 0; i < n; ++i) buf[lslot<true>(i, 1)] = mk(in[2 * i], in[2 * i + 1]);
+  switch (n) {
+    HC_CT(18)
+    HC_CT(24)
+    HC_CT(27)
+    HC_CT(36)
+    HC_CT(48)
+    HC_CT(54)
+    HC_CT(72)
+    HC_CT(81)
+    HC_CT(108)
+    HC_CT(144)
+    HC_CT(162)
+    HC_CT(216)
+    HC_CT(243)
+    HC_CT(288)
+    HC_CT(324)
+    HC_CT(432)
+    HC_CT(486)
+    HC_CT(768)
+    default:
+      return -1;
+  }
+  for (int i = 0; i < n; ++i) {
+    out[2 * i] = buf[lslot<true>(i, 1)].re;
+    out[2 * i + 1] = buf[lslot<true>(i, 1)].im;
+  }
+  return 0;
+}
+
 int hc_ct_plan_check(int n) {
   switch (n) {
     case 16: return ct_plan_check<16>();

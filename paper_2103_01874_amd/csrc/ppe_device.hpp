@@ -99,12 +99,13 @@ struct FftDev {
                            // (global table; kernels stage a copy in LDS)
 };
 
-// Compile-time plan of a power-of-two length N (2 <= N <= 2048), factored as
-// the host factors powers of two: radix-8 stages, then one radix-4 or radix-2
-// stage for the remaining factor.  Stage counts, radices, sub-transform
-// lengths and twiddle steps are constants, so the stage loop unrolls, the
-// radix dispatch folds away and j / ns, j mod ns become shifts.  Only the
-// twiddle table is a run-time value.
+// Compile-time plan of length N.  Stage counts, radices, sub-transform lengths
+// and twiddle steps are constants, so the stage loop unrolls, the radix
+// dispatch folds away and j / ns, j mod ns become shifts and multiplications.
+// Only the twiddle table is a run-time value.  Powers of two and three times a
+// power of two take the host's factors (radix-8 stages and a last radix 4 or
+// 2; a radix-3 stage, then radix 4 and 2); the other products of twos and
+// threes take the radices of kMixedPlans.
 struct StageTab {
   int radix[kMaxStages];
   int ns[kMaxStages];
@@ -152,16 +153,52 @@ constexpr StageTab three_pow2_stages(int n) {
 
 constexpr bool is_pow2_c(int n) { return n >= 1 && (n & (n - 1)) == 0; }
 
+// Two or three stages of radix 6, 9, 12 or 18 instead of the run-time plans'
+// four to six of radix 2, 3 and 4: a stage costs a pass through LDS and two
+// barriers.  E, the elements per thread, is the lcm of the radices and at most
+// 18 (36 doubles of registers).  Against the run-time plans: k_fft_z 36 -> 15 us
+// and k_r2c 25 -> 17.5 at 162x100x216, 29 -> 17 and 32 -> 27.5 at 486x60x144,
+// k_r2c 42 -> 27 at 72x200x81 x 5, every one of 10 -> 7 us at 54x37x48.
+struct MixedPlan {
+  int n, e, nst, radix[4];
+};
+constexpr MixedPlan kMixedPlans[] = {
+    {18, 6, 2, {6, 3}},       {24, 12, 2, {12, 2}},      {27, 9, 2, {9, 3}},       {36, 6, 2, {6, 6}},
+    {48, 12, 2, {12, 4}},     {54, 18, 2, {9, 6}},       {72, 12, 2, {12, 6}},     {81, 9, 2, {9, 9}},
+    {108, 18, 2, {18, 6}},    {144, 12, 2, {12, 12}},    {162, 18, 2, {18, 9}},    {216, 6, 3, {6, 6, 6}},
+    {243, 9, 3, {9, 9, 3}},   {288, 12, 3, {12, 12, 2}}, {324, 18, 2, {18, 18}},   {432, 12, 3, {12, 12, 3}},
+    {486, 18, 3, {18, 9, 3}}, {768, 12, 4, {12, 4, 4, 4}}};
+constexpr MixedPlan mixed_plan(int n) {
+  for (const MixedPlan& p : kMixedPlans)
+    if (p.n == n) return p;
+  return MixedPlan{};
+}
+constexpr StageTab mixed_stages(int n) {
+  StageTab t{};
+  const MixedPlan p = mixed_plan(n);
+  int ns = 1;
+  for (int s = 0; s < p.nst; ++s) {
+    t.radix[s] = p.radix[s];
+    t.ns[s] = ns;
+    t.tstep[s] = n / (ns * p.radix[s]);
+    ns *= p.radix[s];
+  }
+  return t;
+}
+
 template <int N>
 struct CFft {
-  static_assert(N >= 2 && (is_pow2_c(N) || (N % 3 == 0 && N >= 12 && is_pow2_c(N / 3))),
-                "a power of two, or three times a power of two of at least 4");
   static constexpr bool pow2 = is_pow2_c(N);
+  static constexpr bool mixed = mixed_plan(N).n == N;
+  static_assert(N >= 2 && (pow2 || mixed || (N % 3 == 0 && N >= 12 && is_pow2_c(N / 3))),
+                "a power of two, three times a power of two of at least 4, or a length of kMixedPlans");
   static constexpr int n = N;
-  static constexpr int nst = pow2 ? ilog2_c(N) / 3 + (ilog2_c(N) % 3 ? 1 : 0) : 1 + (ilog2_c(N / 3) + 1) / 2;
-  static constexpr int e = pow2 ? (ilog2_c(N) >= 3 ? 8 : N) : 12;  // lcm of the radices
+  static constexpr int nst = mixed  ? mixed_plan(N).nst
+                             : pow2 ? ilog2_c(N) / 3 + (ilog2_c(N) % 3 ? 1 : 0)
+                                    : 1 + (ilog2_c(N / 3) + 1) / 2;
+  static constexpr int e = mixed ? mixed_plan(N).e : pow2 ? (ilog2_c(N) >= 3 ? 8 : N) : 12;  // lcm of the radices
   static constexpr int tc = N / e;
-  static constexpr StageTab tab = pow2 ? pow2_stages(N) : three_pow2_stages(N);
+  static constexpr StageTab tab = mixed ? mixed_stages(N) : pow2 ? pow2_stages(N) : three_pow2_stages(N);
   const double* tw;  // as in FftDev
 };
 
@@ -270,12 +307,73 @@ PPE_HD void dft8(cplx<T>* v) {
   v[7] = b[3];
 }
 
+// Nine points as 3 x 3: w = exp(DIR 2 pi i / 9) between the two passes.
+template <int DIR, typename T>
+PPE_HD void dft9(cplx<T>* v) {
+  const T c1 = T(0.76604444311897803520), s1 = T(0.64278760968653932632);  // 40 degrees
+  const T c2 = T(0.17364817766693034885), s2 = T(0.98480775301220805937);  // 80
+  const T c4 = T(-0.93969262078590838405), s4 = T(0.34202014332566873304); // 160
+  cplx<T> a[9];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {  // x(q + 3 r), r = 0..2
+    cplx<T> t[3] = {v[q], v[q + 3], v[q + 6]};
+    dft3<DIR>(t);
+    for (int k = 0; k < 3; ++k) a[3 * k + q] = t[k];
+  }
+  const T d = T(DIR);
+  a[4] = cmul(a[4], mk(c1, d * s1));
+  a[5] = cmul(a[5], mk(c2, d * s2));
+  a[7] = cmul(a[7], mk(c2, d * s2));
+  a[8] = cmul(a[8], mk(c4, d * s4));
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    cplx<T> t[3] = {a[3 * k], a[3 * k + 1], a[3 * k + 2]};
+    dft3<DIR>(t);
+    for (int m = 0; m < 3; ++m) v[k + 3 * m] = t[m];
+  }
+}
+
+template <int R, int DIR, typename T>
+PPE_HD void dft(cplx<T>* v);
+
+// N1 N2 points, N1 and N2 without a common factor: with inputs at
+// (N2 n1 + N1 n2) mod N and outputs at the k with k mod N1 = k1, k mod N2 = k2
+// the two passes need no twiddles between them (Good and Thomas).
+template <int N1, int N2, int DIR, typename T>
+PPE_HD void dft_coprime(cplx<T>* v) {
+  constexpr int N = N1 * N2;
+  cplx<T> a[N];
+#pragma unroll
+  for (int n1 = 0; n1 < N1; ++n1) {
+    cplx<T> t[N2];
+#pragma unroll
+    for (int n2 = 0; n2 < N2; ++n2) t[n2] = v[(N2 * n1 + N1 * n2) % N];
+    dft<N2, DIR>(t);
+#pragma unroll
+    for (int k2 = 0; k2 < N2; ++k2) a[k2 * N1 + n1] = t[k2];
+  }
+#pragma unroll
+  for (int k2 = 0; k2 < N2; ++k2) {
+    dft<N1, DIR>(&a[k2 * N1]);
+#pragma unroll
+    for (int k1 = 0; k1 < N1; ++k1) {
+      int k = k2;
+      while (k % N1 != k1) k += N2;
+      v[k] = a[k2 * N1 + k1];
+    }
+  }
+}
+
 template <int R, int DIR, typename T>
 PPE_HD void dft(cplx<T>* v) {
   if constexpr (R == 2) dft2<DIR>(v);
   else if constexpr (R == 3) dft3<DIR>(v);
   else if constexpr (R == 4) dft4<DIR>(v);
+  else if constexpr (R == 6) dft_coprime<2, 3, DIR>(v);
   else if constexpr (R == 8) dft8<DIR>(v);
+  else if constexpr (R == 9) dft9<DIR>(v);
+  else if constexpr (R == 12) dft_coprime<4, 3, DIR>(v);
+  else if constexpr (R == 18) dft_coprime<2, 9, DIR>(v);
 }
 
 // LDS slot of element n of a transform.  Rows (es == 1) are padded with one
@@ -341,20 +439,16 @@ PPE_HD cplx<T> tw_load(const double* tw, int ti) {
   return mk(T(tw[2 * ti]), DIR > 0 ? T(-tw[2 * ti + 1]) : T(tw[2 * ti + 1]));
 }
 
-// Stage twiddles w^r, r = 1..R-1, of w = W_n^{jm tstep}: w, w^2 (and w^4 for
-// radix 8) come from the table, the others are products of those (at most
-// two roundings more than a table value).
+// Stage twiddles w^r, r = 1..R-1, of w = W_n^{jm tstep}: w, w^2, w^4, ... come
+// from the table, the others are products of those (one product per further
+// bit of r, each at most two roundings).
 template <int R, int DIR, typename T>
 PPE_HD void stage_twiddles_of(const double* tw, int base, cplx<T>* w) {
-  w[1] = tw_load<DIR, T>(tw, base);
-  if constexpr (R >= 3) w[2] = tw_load<DIR, T>(tw, 2 * base);
-  if constexpr (R == 4) w[3] = cmul(w[1], w[2]);
-  if constexpr (R == 8) {
-    w[3] = cmul(w[1], w[2]);
-    w[4] = tw_load<DIR, T>(tw, 4 * base);
-    w[5] = cmul(w[1], w[4]);
-    w[6] = cmul(w[2], w[4]);
-    w[7] = cmul(w[3], w[4]);
+#pragma unroll
+  for (int r = 1; r < R; ++r) {
+    int h = 1;  // the highest bit of r
+    while (2 * h <= r) h *= 2;
+    w[r] = r == h ? tw_load<DIR, T>(tw, r * base) : cmul(w[r - h], w[h]);
   }
 }
 

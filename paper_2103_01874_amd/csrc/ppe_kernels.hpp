@@ -148,4 +148,13 @@ struct InfoRec {
   double p_mean;
 };
 
+// What block 0 of a forward row transform reduces (finish_block's arguments).
+struct FinishArgs {
+  int nblk;
+  int kind;
+  double tol;
+  double* out;
+  int ostride;
+};
+
 }  // namespace ppe

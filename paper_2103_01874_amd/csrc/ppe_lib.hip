@@ -22,7 +22,7 @@
 #include <vector>
 
 #include "ppe.h"
-#include "ppe_kernels.hpp"
+#include "ppe_fft.hpp"
 #include "ppe_kernels.hip.inc"
 #include "ppe_stencil.hip.inc"
 #include "ppe_predict.hip.inc"
@@ -67,7 +67,7 @@ struct ppe_plan_s {
   int tx = 1;            // kx columns per block (z FFT)
   int txs = 1, pch = 1;  // systems per block, chunks per system (tri)
   int mc = 16;           // register rows per chunk (template of k_tri)
-  int fx_ct = 0, fz_ct = 0;  // lengths with a compile-time FFT plan (0: run-time plan)
+  int fx_ct = 0, fz_ct = 0;  // fft_group of the lengths (0: run-time plan)
   bool tri_refine = false;  // one difference-form refinement step in the y solve
   int spec_chunks = 1;   // kx chunks the spectral chain runs in (see launch_chain)
   int src_pt = 8;        // units per thread of k_source (2, 4 or 8)
@@ -217,13 +217,11 @@ bool shape_plan(ppe_plan_s* p, size_t lds_limit = 65536) {
   const ppe_desc_t& d = p->d;
   if (!fft_factor(d.nx, p->fx) || !fft_factor(d.nz, p->fz)) return false;
   {
-    // compile-time plans: powers of two 16..2048, and 96, 192, 384
-    const auto ct = [](int n) {
-      return ((n >= 16 && n <= 2048 && (n & (n - 1)) == 0) || n == 96 || n == 192 || n == 384) ? n : 0;
-    };
     const bool rt = tune_env("PPE_TUNE_RT_FFT") > 0;  // force the run-time plans
-    p->fx_ct = rt ? 0 : ct(d.nx);
-    p->fz_ct = rt ? 0 : ct(d.nz);
+    p->fx_ct = rt ? 0 : fft_group(d.nx);
+    p->fz_ct = rt ? 0 : fft_group(d.nz);
+    if (p->fx_ct) fft_ct_shape(d.nx, p->fx.e, p->fx.tc);
+    if (p->fz_ct) fft_ct_shape(d.nz, p->fz.e, p->fz.tc);
   }
   Geom& g = p->g;
   g.nx = d.nx;
@@ -262,7 +260,7 @@ bool shape_plan(ppe_plan_s* p, size_t lds_limit = 65536) {
   p->tx = std::min(1 << g.tws, 8);
   if (tune_env("PPE_TUNE_TX") > 0) p->tx = std::min(1 << g.tws, tune_env("PPE_TUNE_TX"));
   while (p->tx > 1 && ((size_t)d.nz * (p->tx + kColPad) * 16 + (size_t)d.nz * 16 > lds_limit ||
-                       p->tx * tcz > ((p->fz_ct && (p->fz_ct & (p->fz_ct - 1)) == 0) ? 1024 : 512)))
+                       p->tx * tcz > (p->fz_ct == 1 ? 1024 : 512)))
     p->tx /= 2;
   // columns + twiddle table (the plane-sum reduction reuses the column area)
   p->lds_z = std::max((size_t)d.nz * (p->tx + kColPad) * 16, (size_t)p->tx * tcz * 8) + (size_t)d.nz * 16;
@@ -502,45 +500,16 @@ Work<TS> make_work(ppe_plan_s* p, int inst0) {
     default: return PPE_ERR_UNSUPPORTED;                \
   }
 
-#define PPE_E_SWITCH(EVAL, CALL)  \
-  switch (EVAL) {                 \
-    case 1: { constexpr int E = 1; CALL; } break;   \
-    case 2: { constexpr int E = 2; CALL; } break;   \
-    case 3: { constexpr int E = 3; CALL; } break;   \
-    case 4: { constexpr int E = 4; CALL; } break;   \
-    case 6: { constexpr int E = 6; CALL; } break;   \
-    case 8: { constexpr int E = 8; CALL; } break;   \
-    case 12: { constexpr int E = 12; CALL; } break; \
-    default: return PPE_ERR_UNSUPPORTED;            \
-  }
-
-// Launch CALL with FV the kernels' FFT plan of the host plan HF and E its
-// elements per thread: a compile-time CFft<N> when CT (the plan's
-// power-of-two length, 16..2048), else the run-time plan.
-#define PPE_FFT_CT_CASE(NN, HF, FV, CALL) \
-  case NN: {                              \
-    constexpr int E = CFft<NN>::e;        \
-    const CFft<NN> FV{(HF).tw};           \
-    CALL;                                 \
-  } break;
-#define PPE_FFT_SWITCH(CT, HF, FV, CALL)                                              \
-  switch (CT) {                                                                     \
-    PPE_FFT_CT_CASE(16, HF, FV, CALL)                                               \
-    PPE_FFT_CT_CASE(32, HF, FV, CALL)                                               \
-    PPE_FFT_CT_CASE(64, HF, FV, CALL)                                               \
-    PPE_FFT_CT_CASE(128, HF, FV, CALL)                                              \
-    PPE_FFT_CT_CASE(256, HF, FV, CALL)                                              \
-    PPE_FFT_CT_CASE(512, HF, FV, CALL)                                              \
-    PPE_FFT_CT_CASE(1024, HF, FV, CALL)                                             \
-    PPE_FFT_CT_CASE(2048, HF, FV, CALL)                                             \
-    PPE_FFT_CT_CASE(96, HF, FV, CALL)                                               \
-    PPE_FFT_CT_CASE(192, HF, FV, CALL)                                              \
-    PPE_FFT_CT_CASE(384, HF, FV, CALL)                                              \
-    default: {                                                                      \
-      const FftDev FV = to_dev(HF);                                                 \
-      PPE_E_SWITCH(FV.e, CALL);                                                     \
-    } break;                                                                        \
-  }
+// CALL(G) with G the FftGroup of group CT in TS.
+#define PPE_FFT_DISPATCH(CT, CALL)                          \
+  [&] {                                                    \
+    switch (CT) {                                          \
+      case 0: { using G = FftGroup<0, TS>; return CALL; }  \
+      case 1: { using G = FftGroup<1, TS>; return CALL; }  \
+      case 2: { using G = FftGroup<2, TS>; return CALL; }  \
+      default: { using G = FftGroup<3, TS>; return CALL; } \
+    }                                                      \
+  }()
 
 hipEvent_t prof_event(ppe_plan_s* p) {
   if (!p->pool.empty()) {
@@ -603,18 +572,11 @@ ppe_status_t launch_fft_z(ppe_plan_s* p, const Work<TS>& W, int nb, int dir, int
   // on a tile; with an odd count the last block is a half tile at hx or the
   // range ends inside a tile, and that block keeps the plain order)
   const int pair = (p->tx * 2 == (1 << g.tws) && g.ny % 8 == 0 && kx0 % (2 * p->tx) == 0) ? 1 : 0;
-  if (dir < 0) {
-    PPE_TIMED(p, "k_fft_z_fwd",
-              PPE_FFT_SWITCH(p->fz_ct, p->fz, fz,
-                             (k_fft_z<TS, E, -1><<<grid, block, p->lds_z, p->stream>>>(g, fz, W, p->tx, check, kx0,
-                                                                                      pair))));
-  } else {
-    PPE_TIMED(p, "k_fft_z_inv",
-              PPE_FFT_SWITCH(p->fz_ct, p->fz, fz,
-                             (k_fft_z<TS, E, +1><<<grid, block, p->lds_z, p->stream>>>(g, fz, W, p->tx, check, kx0,
-                                                                                      pair))));
-  }
-  return PPE_OK;
+  const FftLaunch l{grid, block, p->lds_z, p->stream};
+  bool ok = false;
+  PPE_TIMED(p, dir < 0 ? "k_fft_z_fwd" : "k_fft_z_inv",
+            ok = PPE_FFT_DISPATCH(p->fz_ct, G::fft_z(l, to_dev(p->fz), g, W, p->tx, dir, check, kx0, pair)));
+  return ok ? PPE_OK : PPE_ERR_UNSUPPORTED;
 }
 
 // The spectral chain: forward z FFT, y tridiagonal solves, inverse z FFT.
@@ -678,6 +640,30 @@ void rho_min_pass(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb) {
   PPE_TIMED(p, "k_rho_min_finish", (k_rho_min_finish<<<1, 64, 0, p->stream>>>(tab, p->scal, inst0, nb)));
 }
 
+// Forward row transform of src (FP64, or the spectrum's precision with
+// src_ts), whose block 0 reduces the sums of the kernel before it; inverse row
+// transform to p (mode 0) or onto p (mode 1).
+template <typename TS>
+ppe_status_t launch_r2c(ppe_plan_s* p, const PtrTable& tab, const Work<TS>& W, int nb, const void* src, bool src_ts,
+                        int check, const FinishArgs& fin) {
+  const long long npairs = ((long long)p->g.ny * p->g.nz + 1) / 2;
+  const FftLaunch l{dim3((unsigned)((npairs + p->rp - 1) / p->rp) + 1, 1, nb), dim3(p->rp * p->fx.tc), p->lds_x,
+                    p->stream};
+  bool ok = false;
+  PPE_TIMED(p, "k_r2c",
+            ok = PPE_FFT_DISPATCH(p->fx_ct, G::r2c(l, to_dev(p->fx), tab, p->g, W, src, src_ts, p->rp, check, fin)));
+  return ok ? PPE_OK : PPE_ERR_UNSUPPORTED;
+}
+
+template <typename TS>
+ppe_status_t launch_c2r(ppe_plan_s* p, const PtrTable& tab, const Work<TS>& W, int nb, int mode, int check) {
+  const long long npairs = ((long long)p->g.ny * p->g.nz + 1) / 2;
+  const FftLaunch l{dim3((unsigned)((npairs + p->rp - 1) / p->rp), 1, nb), dim3(p->rp * p->fx.tc), p->lds_x, p->stream};
+  bool ok = false;
+  PPE_TIMED(p, "k_c2r", ok = PPE_FFT_DISPATCH(p->fx_ct, G::c2r(l, to_dev(p->fx), tab, p->g, W, p->rp, mode, check)));
+  return ok ? PPE_OK : PPE_ERR_UNSUPPORTED;
+}
+
 template <typename TS>
 ppe_status_t solve_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb) {
   const Geom& g = p->g;
@@ -685,22 +671,14 @@ ppe_status_t solve_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb) 
   const bool mixed = p->d.precision == PPE_PREC_MIXED;
   const double tol = mixed ? p->d.tol : 0.0;
   rho_min_pass(p, tab, inst0, nb);
-  const long long nrows = (long long)g.ny * g.nz;
-  const long long npairs = (nrows + 1) / 2;
-  dim3 xgrid((unsigned)((npairs + p->rp - 1) / p->rp), 1, nb);
-  dim3 xblock(p->rp * p->fx.tc);
   PPE_TIMED(p, "k_rhs",
             PPE_MARCH_SWITCH(p->mrhs, (k_rhs<TS, true, NT><<<dim3(p->mrhs.grid, 1, nb), NT, march_lds(p->mrhs, 4),
                                                               p->stream>>>(tab, g, p->mrhs.m, W))));
   // (the sums of the kernel before a forward row transform are reduced by its block 0)
-  PPE_TIMED(p, "k_r2c",
-            PPE_FFT_SWITCH(p->fx_ct, p->fx, fx, (k_r2c<TS, E><<<dim3(xgrid.x + 1, 1, nb), xblock, p->lds_x, p->stream>>>(
-                                   tab, g, fx, W, p->b64, p->rp, 0, FinishArgs{p->mrhs.grid, FIN_RHS, tol, nullptr, 0}))));
-  ppe_status_t st = launch_chain<TS>(p, W, nb, 0);
+  ppe_status_t st = launch_r2c<TS>(p, tab, W, nb, p->b64, false, 0, FinishArgs{p->mrhs.grid, FIN_RHS, tol, nullptr, 0});
+  if (st == PPE_OK) st = launch_chain<TS>(p, W, nb, 0);
+  if (st == PPE_OK) st = launch_c2r<TS>(p, tab, W, nb, 0, 0);
   if (st != PPE_OK) return st;
-  PPE_TIMED(p, "k_c2r",
-            PPE_FFT_SWITCH(p->fx_ct, p->fx, fx, (k_c2r<TS, E><<<xgrid, xblock, p->lds_x, p->stream>>>(
-                                   tab, g, fx, W, p->rp, 0, 0))));
   if (mixed) {
     // the refinement residual in the spectrum's precision (the first half of
     // the FP64 residual buffer)
@@ -710,14 +688,10 @@ ppe_status_t solve_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb) 
                 PPE_PPT_SWITCH(p->mrs.ppt, (k_resid<TS, PPT><<<dim3(p->mrs.grid, 1, nb), kMarchThreads,
                                                                march_lds(p->mrs, 1), p->stream>>>(
                                                 tab, g, p->mrs.m, W, rs))));
-      PPE_TIMED(p, "k_r2c",
-                PPE_FFT_SWITCH(p->fx_ct, p->fx, fx, (k_r2c<TS, E><<<dim3(xgrid.x + 1, 1, nb), xblock, p->lds_x, p->stream>>>(
-                                       tab, g, fx, W, static_cast<const TS*>(rs), p->rp, 1, FinishArgs{p->mrs.grid, FIN_RESID, 0.0, nullptr, 0}))));
-      st = launch_chain<TS>(p, W, nb, 1);
+      st = launch_r2c<TS>(p, tab, W, nb, rs, true, 1, FinishArgs{p->mrs.grid, FIN_RESID, 0.0, nullptr, 0});
+      if (st == PPE_OK) st = launch_chain<TS>(p, W, nb, 1);
+      if (st == PPE_OK) st = launch_c2r<TS>(p, tab, W, nb, 1, 1);
       if (st != PPE_OK) return st;
-      PPE_TIMED(p, "k_c2r",
-                PPE_FFT_SWITCH(p->fx_ct, p->fx, fx, (k_c2r<TS, E><<<xgrid, xblock, p->lds_x, p->stream>>>(
-                                       tab, g, fx, W, p->rp, 1, 1))));
     }
   }
   return hipGetLastError() == hipSuccess ? PPE_OK : PPE_ERR_DEVICE;
@@ -733,10 +707,6 @@ ppe_status_t varcoef_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb
   const Geom& g = p->g;
   Work<TS> W = make_work<TS>(p, inst0);
   rho_min_pass(p, tab, inst0, nb);
-  const long long nrows = (long long)g.ny * g.nz;
-  const long long npairs = (nrows + 1) / 2;
-  dim3 xgrid((unsigned)((npairs + p->rp - 1) / p->rp), 1, nb);
-  dim3 xblock(p->rp * p->fx.tc);
   PPE_TIMED(p, "k_rhs",
             PPE_MARCH_SWITCH(p->mrhs, (k_rhs<TS, false, NT><<<dim3(p->mrhs.grid, 1, nb), NT,
                                                                march_lds(p->mrhs, 0), p->stream>>>(tab, g,
@@ -784,13 +754,11 @@ ppe_status_t varcoef_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb
       finish(p, tab, inst0, nb, p->mres.grid, FIN_RESID_LAST, 1, 0.0, h, hs);
       break;
     }
-    PPE_TIMED(p, "k_r2c",
-              PPE_FFT_SWITCH(p->fx_ct, p->fx, fx, (k_r2c<TS, E><<<dim3(xgrid.x + 1, 1, nb), xblock, p->lds_x, p->stream>>>(
-                                     tab, g, fx, W, p->r64, p->rp, 1, FinishArgs{p->mres.grid, FIN_RESID, 0.0, h, hs}))));
-    ppe_status_t st = launch_chain<TS>(p, W, nb, 1);
+    ppe_status_t st =
+        launch_r2c<TS>(p, tab, W, nb, p->r64, false, 1, FinishArgs{p->mres.grid, FIN_RESID, 0.0, h, hs});
+    if (st == PPE_OK) st = launch_chain<TS>(p, W, nb, 1);
+    if (st == PPE_OK) st = launch_c2r<TS>(p, tab, W, nb, 1, 1);
     if (st != PPE_OK) return st;
-    PPE_TIMED(p, "k_c2r",
-              PPE_FFT_SWITCH(p->fx_ct, p->fx, fx, (k_c2r<TS, E><<<xgrid, xblock, p->lds_x, p->stream>>>(tab, g, fx, W, p->rp, 1, 1))));
   }
   return hipGetLastError() == hipSuccess ? PPE_OK : PPE_ERR_DEVICE;
 }
@@ -831,43 +799,12 @@ bool ptrs_ok(const void* const* a, int n) {
 
 namespace {
 // Dynamic LDS above 64 KiB must be enabled per kernel (all z-FFT variants).
-template <typename TS, int E, typename F = FftDev>
-hipError_t allow_big_lds_e(int bytes) {
-  const void* fns[] = {reinterpret_cast<const void*>(&k_fft_z<TS, E, -1, F>),
-                       reinterpret_cast<const void*>(&k_fft_z<TS, E, +1, F>)};
-  for (const void* f : fns) {
-    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
 template <typename TS>
-hipError_t allow_big_lds_t(int bytes) {
-  hipError_t e = hipSuccess;
-  if (e == hipSuccess) e = allow_big_lds_e<TS, 1>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, 2>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, 3>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, 4>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, 6>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, 8>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, 12>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, CFft<16>::e, CFft<16>>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, CFft<32>::e, CFft<32>>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, CFft<64>::e, CFft<64>>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, CFft<128>::e, CFft<128>>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, CFft<256>::e, CFft<256>>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, CFft<512>::e, CFft<512>>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, CFft<1024>::e, CFft<1024>>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, CFft<2048>::e, CFft<2048>>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, CFft<96>::e, CFft<96>>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, CFft<192>::e, CFft<192>>(bytes);
-  if (e == hipSuccess) e = allow_big_lds_e<TS, CFft<384>::e, CFft<384>>(bytes);
-  return e;
+bool allow_big_lds_t(int bytes) {
+  return FftGroup<0, TS>::allow_lds(bytes) && FftGroup<1, TS>::allow_lds(bytes) &&
+         FftGroup<2, TS>::allow_lds(bytes) && FftGroup<3, TS>::allow_lds(bytes);
 }
-hipError_t allow_big_lds(int bytes) {
-  hipError_t e = allow_big_lds_t<double>(bytes);
-  return e == hipSuccess ? allow_big_lds_t<float>(bytes) : e;
-}
+bool allow_big_lds(int bytes) { return allow_big_lds_t<double>(bytes) && allow_big_lds_t<float>(bytes); }
 
 }  // namespace
 
@@ -896,7 +833,7 @@ void* scratch_on(int dev) {
   if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return nullptr;
   int lds_max = 65536;
   if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return nullptr;
-  if (lds_max > 65536 && allow_big_lds(lds_max) != hipSuccess) return nullptr;
+  if (lds_max > 65536 && !allow_big_lds(lds_max)) return nullptr;
   g_scratch_ptr[dev] = ptr;
   return ptr;
 }
@@ -964,7 +901,7 @@ ppe_status_t ppe_plan(const ppe_desc_t* desc, void* stream, ppe_plan_t* out) {
     delete p;
     return PPE_ERR_UNSUPPORTED;
   }
-  if (p->lds_z > 65536 && allow_big_lds((int)p->lds_z) != hipSuccess) {
+  if (p->lds_z > 65536 && !allow_big_lds((int)p->lds_z)) {
     delete p;
     return PPE_ERR_DEVICE;
   }

@@ -216,3 +216,29 @@ def test_fftz_pair_order_is_a_permutation_with_paired_halves(hc, gx, gy):
     for t in range(gy // 2):
         a, b = where[(2 * t) * gx + np.arange(gx)], where[(2 * t + 1) * gx + np.arange(gx)]
         assert np.array_equal(b, a + 8)
+
+
+MIXED = [18, 24, 27, 36, 48, 54, 72, 81, 108, 144, 162, 216, 243, 288, 324, 432, 486, 768]
+
+
+@pytest.mark.parametrize("n", MIXED)
+def test_mixed_radix_plans_match_numpy(hc, n):
+    """The compile-time plans of radix 6, 9, 12 and 18 stages, both ways, and
+    no further from an extended-precision transform than the run-time plan of
+    the same length (its error plus the rounding of one stage)."""
+    f = hc.hc_fft_mixed
+    f.argtypes = hc.hc_fft.argtypes
+    rng = np.random.default_rng(300 + n)
+    x = rng.standard_normal(n) + 1j * rng.standard_normal(n)
+    xin = np.ascontiguousarray(np.stack([x.real, x.imag], -1).ravel())
+    k = np.arange(n)
+    ang = (np.outer(k, k) % n).astype(np.longdouble) * (2 * (np.arctan(np.longdouble(1)) * 4) / n)
+    for d in (-1, +1):
+        re = np.cos(ang) @ x.real.astype(np.longdouble) - d * (np.sin(ang) @ x.imag.astype(np.longdouble))
+        im = np.cos(ang) @ x.imag.astype(np.longdouble) + d * (np.sin(ang) @ x.real.astype(np.longdouble))
+        err = []
+        for fn in (f, hc.hc_fft):
+            out = np.zeros(2 * n)
+            assert fn(n, d, _p(xin), _p(out)) == 0
+            err.append(float(np.sqrt(((out[0::2] - re) ** 2 + (out[1::2] - im) ** 2).sum() / (re ** 2 + im ** 2).sum())))
+        assert err[0] <= err[1] + 2.3e-16, err
