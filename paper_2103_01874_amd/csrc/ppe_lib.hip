@@ -77,7 +77,6 @@ struct ppe_plan_s {
   struct MarchCfg {
     March m;
     int grid = 0;    // blocks per instance
-    int ppt = 1;     // interior points per thread per plane (kernel template)
     int nt = 256;    // threads per block (kernel template: 256, 512 or 1024)
     int tslots = 0;  // LDS slots of a tile plane with its halo ring
   } mrhs, mcor, mres, mrs;  // mres: k_resid_var; mrs: the refinement residual k_resid
@@ -142,13 +141,11 @@ size_t spec_elem_bytes(const ppe_desc_t* d) {
   return d->precision == PPE_PREC_FP64 ? 2 * sizeof(double) : 2 * sizeof(float);
 }
 
-// Tile of a marching stencil kernel run by `nt` threads per block: TXT = nx
-// when nx <= max_txt, else the largest divisor of nx up to max_txt; TJ rows so
-// that a tile plane has about `points` interior cells and its halo ring at most
-// `ring` points; KC planes per chunk, at most max_planes.
-bool march_shape(const ppe_desc_t& d, int points, int max_txt, const char* env, ppe_plan_s::MarchCfg& c,
-                 int nt = kMarchThreads, int max_planes = 16, int ring = kRingPT * kMarchThreads, int blocks = 2048,
-                 bool xcd_bands = true) {
+// Tile of a marching stencil kernel run by `nt` threads per block, one point
+// each: TXT = nx when nx <= max_txt, else the largest divisor of nx up to
+// max_txt; TJ rows so that a tile plane fills the block and its halo ring has
+// at most `nt` points; KC planes per chunk, at most max_planes.
+bool march_shape(const ppe_desc_t& d, int max_txt, const char* env, ppe_plan_s::MarchCfg& c, int nt, int max_planes) {
   March& M = c.m;
   c.nt = nt;
   if (tune_env("PPE_TUNE_TXT") > 0) max_txt = tune_env("PPE_TUNE_TXT");
@@ -161,34 +158,29 @@ bool march_shape(const ppe_desc_t& d, int points, int max_txt, const char* env, 
         break;
       }
   }
-  M.tj = std::max(1, std::min(points / M.txt, d.ny));
+  M.tj = std::max(1, std::min(nt / M.txt, d.ny));
   if (tune_env(env) > 0) M.tj = std::max(1, std::min(tune_env(env), d.ny));
-  while (M.tj > 1 && 2 * M.txt + 2 * M.tj > ring) --M.tj;
-  if ((long long)M.tj * M.txt > (long long)nt * kMaxPPT) return false;
+  while (M.tj > 1 && 2 * M.txt + 2 * M.tj > nt) --M.tj;
+  if (M.tj * M.txt > nt || 2 * (M.txt + M.tj) > nt) return false;
   M.ntx = d.nx / M.txt;
   M.ntj = (d.ny + M.tj - 1) / M.tj;
-  // Chunks of planes.  The residual passes: about `blocks` blocks an instance.
-  // k_rhs and k_correct (blocks = 0): a block pays about 0.7 of a plane for the
-  // planes at its ends, and a grid of a few blocks per CU should load the CUs
-  // evenly, with at least two on each for their loads to overlap (64x64x64 x 8
-  // k_correct 48 -> 40 us, 128x512x96 121 -> 111 against 2048 blocks an instance).
+  // Chunks of planes: a block pays about 0.7 of a plane for the planes at its
+  // ends, and a grid of a few blocks per CU should load the CUs evenly, with at
+  // least two on each for their loads to overlap (64x64x64 x 8 k_correct 48 ->
+  // 40 us, k_resid 16.3 -> 14.1, 128x512x96 k_correct 121 -> 111 against 2048
+  // blocks an instance).
   const int ntile = M.ntx * M.ntj;
   if (tune_env("PPE_TUNE_MAX_PLANES") > 0) max_planes = tune_env("PPE_TUNE_MAX_PLANES");
   int nkc = (d.nz + max_planes - 1) / max_planes;
-  if (blocks > 0) {
-    nkc = std::min(std::max(nkc, (blocks + ntile - 1) / ntile), std::max(1, d.nz / 2));
-    M.kc = (d.nz + nkc - 1) / nkc;
-  } else {
-    M.kc = d.nz;
-    double best = 0.0;
-    for (; nkc <= std::max(1, d.nz / 2); ++nkc) {
-      const int kc = (d.nz + nkc - 1) / nkc;
-      const double per_cu = (double)ntile * d.batch * ((d.nz + kc - 1) / kc) / 256.0;
-      const double score = per_cu / std::ceil(per_cu) * std::min(1.0, per_cu / 2.0) * kc / (kc + 0.7);
-      if (score > best * 1.001) {
-        best = score;
-        M.kc = kc;
-      }
+  M.kc = d.nz;
+  double best = 0.0;
+  for (; nkc <= std::max(1, d.nz / 2); ++nkc) {
+    const int kc = (d.nz + nkc - 1) / nkc;
+    const double per_cu = (double)ntile * d.batch * ((d.nz + kc - 1) / kc) / 256.0;
+    const double score = per_cu / std::ceil(per_cu) * std::min(1.0, per_cu / 2.0) * kc / (kc + 0.7);
+    if (score > best * 1.001) {
+      best = score;
+      M.kc = kc;
     }
   }
   M.nkc = (d.nz + M.kc - 1) / M.kc;
@@ -200,12 +192,9 @@ bool march_shape(const ppe_desc_t& d, int points, int max_txt, const char* env, 
   // by where the arrays lie, -> 1126; 384x192x324: 331 -> 323 and 459 -> 443).
   // Planes of few tiles keep the ranges: bands of one or two tile rows re-read
   // more halo rows than they hold (96x64x96 x 12, 26 tiles: 95 -> 105 us).
-  const int bands = tune_env("PPE_TUNE_BANDS") > 0 ? tune_env("PPE_TUNE_BANDS") : (xcd_bands && ntile >= 64 ? 16 : 1);
+  const int bands = tune_env("PPE_TUNE_BANDS") > 0 ? tune_env("PPE_TUNE_BANDS") : (ntile >= 64 ? 16 : 1);
   M.run = bands > 1 ? std::max(1, ntile / bands) : (M.nt + 7) / 8;
   c.grid = 8 * M.run * (((M.nt + M.run - 1) / M.run + 7) / 8);
-  const int npt = M.txt * M.tj;
-  c.ppt = 1;
-  while (c.ppt * nt < npt) c.ppt *= 2;
   c.tslots = (M.txt + 2) * (M.tj + 2);
   return true;
 }
@@ -322,9 +311,9 @@ bool shape_plan(ppe_plan_s* p, size_t lds_limit = 65536) {
   // are whole wavefronts (256x256x256: 213 against 224; rows of 48 cells leave
   // threads idle, 96x64x96 x 12: 99 against 88).  A block marches at most 16
   // planes; 32 on planes of 128 K cells, and in k_correct's small tiles (a
-  // 256x128x256 step 401.6 against 403.5 us: the k_rhs that follows is faster).  The
-  // residual passes take 64 x 8 tiles, two points per thread, on the planes of
-  // k_correct's (k_resid_var) or on all (k_resid).
+  // 256x128x256 step 401.6 against 403.5 us: the k_rhs that follows is faster).
+  // The residual passes take 512 threads throughout (256x128x256 k_resid_var
+  // 54.3 against 55.3 us, 64x64x64 x 8 k_resid 14.1 against 17.1).
   const auto nt_of = [](const char* env, int def) {
     const int v = tune_env(env);
     return (v == 256 || v == 512) ? v : def;
@@ -337,15 +326,11 @@ bool shape_plan(ppe_plan_s* p, size_t lds_limit = 65536) {
   const int planes = plane_cells >= 131072 ? 32 : 16;
   const int planes_cor =
       tune_env("PPE_TUNE_MAX_PLANES_COR") > 0 ? tune_env("PPE_TUNE_MAX_PLANES_COR") : (big_cor ? planes : 32);
-  if (!march_shape(d, nt_rhs, 64, "PPE_TUNE_TJ_RHS", p->mrhs, nt_rhs, planes, nt_rhs, 0) ||
-      !march_shape(d, nt_cor, 64, "PPE_TUNE_TJ_COR", p->mcor, nt_cor, planes_cor, nt_cor, 0) ||
-      !march_shape(d, big_cor ? 512 : 256, 64, "PPE_TUNE_TJ_RES", p->mres) ||
-      // the refinement residual: 64 x 8 tiles at every plane size (against
-      // 64 x 4 below 64 K cells: 7-17% faster from 64^3 to 256 x 128 x 256)
-      // (one range per XCD: 512x256x512 258 against 263 us)
-      !march_shape(d, 512, 64, "PPE_TUNE_TJ_RS", p->mrs, kMarchThreads, 16, kRingPT * kMarchThreads, 2048, false))
+  if (!march_shape(d, 64, "PPE_TUNE_TJ_RHS", p->mrhs, nt_rhs, planes) ||
+      !march_shape(d, 64, "PPE_TUNE_TJ_COR", p->mcor, nt_cor, planes_cor) ||
+      !march_shape(d, 64, "PPE_TUNE_TJ_RES", p->mres, 512, 16) || !march_shape(d, 64, "PPE_TUNE_TJ_RS", p->mrs, 512, 16))
     return false;
-  if (p->mrhs.ppt != 1 || p->mcor.ppt != 1 || (size_t)6 * p->mcor.tslots * 8 > 65536) return false;
+  if ((size_t)6 * p->mcor.tslots * 8 > 65536) return false;
   // per-instance partial-sum stride: the largest grid.x of a reducing kernel
   const long long nrows = (long long)d.ny * d.nz;
   const long long xgrid = (nrows + 1) / 2;  // bound on the row-pair grids, whatever the launch shape
@@ -486,17 +471,6 @@ Work<TS> make_work(ppe_plan_s* p, int inst0) {
   w.nt_rows = nt == 1 ? 1 : (nt == 2 ? 0 : (p->spec_chunks > 1 ? 1 : 0));
   return w;
 }
-
-// ---------------------------------------------------------------------------
-// E dispatch for the FFT kernels
-// ---------------------------------------------------------------------------
-#define PPE_PPT_SWITCH(PVAL, CALL)                  \
-  switch (PVAL) {                                   \
-    case 1: { constexpr int PPT = 1; CALL; } break; \
-    case 2: { constexpr int PPT = 2; CALL; } break; \
-    case 4: { constexpr int PPT = 4; CALL; } break; \
-    default: return PPE_ERR_UNSUPPORTED;            \
-  }
 
 // Launch CALL with NT the threads per block of launch shape CFG (k_rhs and
 // k_correct: one point per thread).
@@ -692,8 +666,7 @@ ppe_status_t solve_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb) 
     TS* rs = reinterpret_cast<TS*>(p->r64);
     for (int it = 0; it < p->d.max_refine; ++it) {
       PPE_TIMED(p, "k_resid",
-                PPE_PPT_SWITCH(p->mrs.ppt, (k_resid<TS, PPT><<<dim3(p->mrs.grid, 1, nb), kMarchThreads,
-                                                               march_lds(p->mrs, 1), p->stream>>>(
+                PPE_MARCH_SWITCH(p->mrs, (k_resid<TS, NT><<<dim3(p->mrs.grid, 1, nb), NT, march_lds(p->mrs, 2), p->stream>>>(
                                                 tab, g, p->mrs.m, W, rs))));
       st = launch_r2c<TS>(p, tab, W, nb, rs, true, 1, FinishArgs{p->mrs.grid, FIN_RESID, 0.0, nullptr, 0});
       if (st == PPE_OK) st = launch_chain<TS>(p, W, nb, 1);
@@ -748,13 +721,11 @@ ppe_status_t varcoef_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb
     }
     if (it == 0)
       PPE_TIMED(p, "k_resid_var",
-                PPE_PPT_SWITCH(p->mres.ppt, (k_resid_var<TS, PPT, 1><<<dim3(p->mres.grid, 1, nb), kMarchThreads,
-                                                                         march_lds(p->mres, 2), p->stream>>>(
+                PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 1, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4), p->stream>>>(
                                                 tab, g, p->mres.m, W, p->r64, 1))));
     else
       PPE_TIMED(p, "k_resid_var",
-                PPE_PPT_SWITCH(p->mres.ppt, (k_resid_var<TS, PPT, 0><<<dim3(p->mres.grid, 1, nb), kMarchThreads,
-                                                                          march_lds(p->mres, 2), p->stream>>>(
+                PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 0, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4), p->stream>>>(
                                                 tab, g, p->mres.m, W, p->r64, 1))));
     double* const h = h0 ? h0 + it : nullptr;
     if (it == max_iters) {
@@ -783,13 +754,11 @@ ppe_status_t defect_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb,
                                                                march_lds(p->mrhs, 0), p->stream>>>(tab, p->g,
                                                                                                    p->mrhs.m, W))));
   PPE_TIMED(p, "k_resid_var",
-            PPE_PPT_SWITCH(p->mres.ppt, (k_resid_var<TS, PPT, 2><<<dim3(p->mres.grid, 1, nb), kMarchThreads,
-                                                                   march_lds(p->mres, 2), p->stream>>>(
+            PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 2, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4), p->stream>>>(
                                             tab, p->g, p->mres.m, W, p->r64, 0))));
   finish(p, tab, inst0, nb, p->mres.grid, FIN_DEFECT, 0, 0.0, out + 2 * (size_t)inst0, 2);
   PPE_TIMED(p, "k_resid_var",
-            PPE_PPT_SWITCH(p->mres.ppt, (k_resid_var<TS, PPT, 0><<<dim3(p->mres.grid, 1, nb), kMarchThreads,
-                                                                   march_lds(p->mres, 2), p->stream>>>(
+            PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 0, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4), p->stream>>>(
                                             tab, p->g, p->mres.m, W, p->r64, 0))));
   finish(p, tab, inst0, nb, p->mres.grid, FIN_DEFECT, 0, 0.0, out + 2 * (size_t)inst0 + 1, 2);
   return hipGetLastError() == hipSuccess ? PPE_OK : PPE_ERR_DEVICE;

@@ -14,7 +14,7 @@ import pytest
 import oracle as O
 import parity_util as PU
 from paper_2103_01874_amd import binding, synth
-from test_gpu_configs import assembly_bound
+from test_gpu_configs import assembly_bound, run_single
 from test_gpu_varcoef import gpu_varcoef, oracle_fp
 
 pytestmark = pytest.mark.gpu
@@ -89,3 +89,20 @@ def test_statistics_of_a_batch_equal_single_runs(precision):
             assert np.allclose(hist[i], h1[0], rtol=1e-9, atol=0.0)
             assert all(close(outs[i]["info"][k], o1[0]["info"][k]) for k in ("res_rel", "div_l2", "div_max", "div0_l2"))
     assert len({r["iters"] for r in recs}) > 1
+
+
+@pytest.mark.parametrize("ybc", [0, 1])
+@pytest.mark.parametrize("shape", [(2, 3, 4), (72, 29, 18), (128, 130, 6), (96, 131, 6)])
+def test_residual_marches_at_tile_edges(shape, ybc):
+    """k_resid and k_resid_var where a tile has no second row of tiles, a
+    remainder of rows or planes, few columns: two fixed-point sweeps and a
+    refined mixed step against the oracle."""
+    pr = synth.random_problem(*shape, seed=9900 + sum(shape), ybc=ybc)
+    (p,), (rec,), H, _ = gpu_varcoef([pr], 2, 0.0)
+    _, ref = oracle_fp(pr, 2)
+    assert PU.rel(p, ref["p"]) <= 1e-12
+    r = np.array(ref["res"])
+    big = r > 1e-9
+    assert np.all(np.abs(H[0][big] - r[big]) <= 1e-8 * r[big])
+    got, rec = run_single(pr, binding.PPE_PREC_MIXED, 3, tol=1e-13)
+    PU.check(pr, got, rec, PU.oracle_step(pr), label=f"{shape} ybc={ybc} ")
