@@ -74,6 +74,7 @@ struct Geom {
   int ybc;              // 0: zero-flux faces at both y ends; 1: outflow top (p = 0 on the face)
   int tws;              // log2 of the spectrum tile width (128-byte tiles of kx)
   long long npts;       // nx*ny*nz
+  long long trows;      // rows (kz, j) of a spectrum tile, padding included
   long long spec_elems; // ntiles * nz * ny * tile width (>= hx * ny * nz)
   double dx, dy, dz;    // cell sizes
   double idx, idy, idz; // 1/dx, 1/dy, 1/dz
@@ -88,7 +89,7 @@ struct Geom {
 // ny * 2^tws values.  `row` = kz * ny + j.
 __host__ __device__ __forceinline__ long long sidx(const Geom& g, int kx, long long row) {
   const long long t = kx >> g.tws;
-  return ((t * g.nz * g.ny + row) << g.tws) + (kx & ((1 << g.tws) - 1));
+  return ((t * g.trows + row) << g.tws) + (kx & ((1 << g.tws) - 1));
 }
 
 // The tile shift of a spectrum of TS values, as a constant (g.tws at run time).
@@ -99,7 +100,7 @@ template <typename TS>
 __host__ __device__ __forceinline__ long long sidx_t(const Geom& g, int kx, long long row) {
   constexpr int sh = kTileShift<TS>;
   const long long t = kx >> sh;
-  return ((t * g.nz * g.ny + row) << sh) + (kx & ((1 << sh) - 1));
+  return ((t * g.trows + row) << sh) + (kx & ((1 << sh) - 1));
 }
 
 // Workspace seen by the kernels (device pointers, per-instance strides).

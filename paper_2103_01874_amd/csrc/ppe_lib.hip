@@ -221,7 +221,15 @@ bool shape_plan(ppe_plan_s* p, size_t lds_limit = 65536) {
   g.tws = d.precision == PPE_PREC_FP64 ? 3 : 4;  // 128-byte kx tiles
   g.npts = (long long)d.nx * d.ny * d.nz;
   const long long ntile = (g.hx + (1 << g.tws) - 1) >> g.tws;
-  g.spec_elems = (ntile << g.tws) * d.ny * d.nz;
+  // Tiles of a spectrum of 64 MiB and more lie a page and two lines further
+  // apart than their rows: a power of two apart, the tiles that a row transform
+  // writes and the z blocks of neighbouring tiles share channels (forward z
+  // 224 -> 204 us at 512x256x512, 150 -> 134 at 192x96x192 x 12; k_c2r 62 -> 48 at
+  // 512x128x256, 33 -> 29 at 256x128x256; 17 to 49 rows equal, 8 and 64 as
+  // none).  Smaller spectra measured the same either way (96x64x96 x 12).
+  g.trows = (long long)d.ny * d.nz;
+  if ((double)d.batch * ntile * g.trows * 128.0 >= 64.0 * 1048576.0) g.trows += 34;
+  g.spec_elems = (ntile << g.tws) * g.trows;
   const double dx = d.lx / d.nx, dy = d.ly / d.ny, dz = d.lz / d.nz;
   g.dx = dx;
   g.dy = dy;

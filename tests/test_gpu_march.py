@@ -106,3 +106,27 @@ def test_residual_marches_at_tile_edges(shape, ybc):
     assert np.all(np.abs(H[0][big] - r[big]) <= 1e-8 * r[big])
     got, rec = run_single(pr, binding.PPE_PREC_MIXED, 3, tol=1e-13)
     PU.check(pr, got, rec, PU.oracle_step(pr), label=f"{shape} ybc={ybc} ")
+
+
+@pytest.mark.parametrize("precision,batch", [(binding.PPE_PREC_FP64, 8), (binding.PPE_PREC_MIXED, 13)])
+def test_padded_spectrum_tiles_equal_unpadded(precision, batch):
+    """A batch whose spectrum passes 64 MiB (its tiles lie further apart)
+    gives the fields of each instance alone (tiles end to end), bit for bit."""
+    import torch
+    prs = [synth.random_problem(128, 64, 128, seed=9950 + i, ybc=1) for i in range(3)]
+    kw = dict(precision=precision, tol=1e-12, max_refine=1, ybc=1)
+    pr = prs[0]
+    plan = binding.Plan(pr.nx, pr.ny, pr.nz, pr.lx, pr.ly, pr.lz, batch=batch, **kw)
+    f = [binding.to_device(p) for p in prs]
+    outs, _ = binding.step(plan, [f[i % 3] for i in range(batch)], [prs[i % 3].rho0 for i in range(batch)],
+                           [pr.dt] * batch)
+    torch.cuda.synchronize()
+    plan.close()
+    for i in range(3):
+        one = binding.Plan(pr.nx, pr.ny, pr.nz, pr.lx, pr.ly, pr.lz, **kw)
+        (alone,), _ = binding.step(one, [f[i]], [prs[i].rho0], [pr.dt])
+        torch.cuda.synchronize()
+        one.close()
+        for n in range(i, batch, 3):
+            for k in ("p", "u", "v", "w"):
+                assert torch.equal(outs[n][k], alone[k]), (n, k)
