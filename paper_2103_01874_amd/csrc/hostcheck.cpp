@@ -222,7 +222,6 @@ int hc_fft_ct(int n, int dir, const double* in, double* out) {
   return 0;
 }
 
-// 0 if the compile-time plan of n equals the host factorisation.
 // The transform of a length of kMixedPlans through its compile-time plan.
 int hc_fft_mixed(int n, int dir, const double* in, double* out) {
   std::vector<double> tw = twiddles(n);
@@ -257,6 +256,14 @@ int hc_fft_mixed(int n, int dir, const double* in, double* out) {
   return 0;
 }
 
+// Planes per record and per block of a marching kernel.
+void hc_march_chunks(int ntile, int nz, int nb, int max_planes, int* kr, int* kc) {
+  const MarchChunks m = march_chunks(ntile, nz, nb, max_planes);
+  *kr = m.kr;
+  *kc = m.kc;
+}
+
+// 0 if the compile-time plan of n equals the host factorisation.
 int hc_ct_plan_check(int n) {
   switch (n) {
     case 16: return ct_plan_check<16>();

@@ -77,7 +77,7 @@ struct ppe_plan_s {
   struct MarchCfg {
     March m;
     int grid = 0;    // blocks per instance
-    int nt = 256;    // threads per block (kernel template: 256, 512 or 1024)
+    int nt = 256;    // threads per block (kernel template: 256 or 512)
     int tslots = 0;  // LDS slots of a tile plane with its halo ring
   } mrhs, mcor, mres, mrs;  // mres: k_resid_var; mrs: the refinement residual k_resid
   double* r64 = nullptr;   // refinement / fixed-point residual (mixed, or PPE_FLAG_VARCOEF)
@@ -164,25 +164,13 @@ bool march_shape(const ppe_desc_t& d, int max_txt, const char* env, ppe_plan_s::
   if (M.tj * M.txt > nt || 2 * (M.txt + M.tj) > nt) return false;
   M.ntx = d.nx / M.txt;
   M.ntj = (d.ny + M.tj - 1) / M.tj;
-  // Chunks of planes: a block pays about 0.7 of a plane for the planes at its
-  // ends, and a grid of a few blocks per CU should load the CUs evenly, with at
-  // least two on each for their loads to overlap (64x64x64 x 8 k_correct 48 ->
-  // 40 us, k_resid 16.3 -> 14.1, 128x512x96 k_correct 121 -> 111 against 2048
-  // blocks an instance).
   const int ntile = M.ntx * M.ntj;
   if (tune_env("PPE_TUNE_MAX_PLANES") > 0) max_planes = tune_env("PPE_TUNE_MAX_PLANES");
-  int nkc = (d.nz + max_planes - 1) / max_planes;
-  M.kc = d.nz;
-  double best = 0.0;
-  for (; nkc <= std::max(1, d.nz / 2); ++nkc) {
-    const int kc = (d.nz + nkc - 1) / nkc;
-    const double per_cu = (double)ntile * d.batch * ((d.nz + kc - 1) / kc) / 256.0;
-    const double score = per_cu / std::ceil(per_cu) * std::min(1.0, per_cu / 2.0) * kc / (kc + 0.7);
-    if (score > best * 1.001) {
-      best = score;
-      M.kc = kc;
-    }
-  }
+  const MarchChunks mc = march_chunks(ntile, d.nz, std::min(d.batch, kMaxLaunch), max_planes);
+  M.kr = mc.kr;
+  M.kc = mc.kc;
+  M.rpb = M.kc / M.kr;
+  M.nrec = ntile * ((d.nz + M.kr - 1) / M.kr);
   M.nkc = (d.nz + M.kc - 1) / M.kc;
   M.nt = M.ntx * M.ntj * M.nkc;
   // Runs of a sixteenth of a plane's tiles: the XCDs march the same planes, each
@@ -197,6 +185,12 @@ bool march_shape(const ppe_desc_t& d, int max_txt, const char* env, ppe_plan_s::
   c.grid = 8 * M.run * (((M.nt + M.run - 1) / M.run + 7) / 8);
   c.tslots = (M.txt + 2) * (M.tj + 2);
   return true;
+}
+
+// LDS of a marching kernel holding `fields` row arrays, and of its block's
+// records of `sums` values a wavefront
+size_t march_lds(const ppe_plan_s::MarchCfg& c, int fields, int sums) {
+  return ((size_t)fields * c.tslots + (size_t)sums * c.m.rpb * (c.nt / 64)) * 8;
 }
 
 // Launch shapes and workspace sizes; fills p (no allocation).  `lds_limit`
@@ -338,12 +332,12 @@ bool shape_plan(ppe_plan_s* p, size_t lds_limit = 65536) {
       !march_shape(d, 64, "PPE_TUNE_TJ_COR", p->mcor, nt_cor, planes_cor) ||
       !march_shape(d, 64, "PPE_TUNE_TJ_RES", p->mres, 512, 16) || !march_shape(d, 64, "PPE_TUNE_TJ_RS", p->mrs, 512, 16))
     return false;
-  if ((size_t)6 * p->mcor.tslots * 8 > 65536) return false;
-  // per-instance partial-sum stride: the largest grid.x of a reducing kernel
+  if (march_lds(p->mcor, 6, 4) > 65536) return false;
+  // per-instance partial-sum stride: the most records of a reducing kernel
   const long long nrows = (long long)d.ny * d.nz;
   const long long xgrid = (nrows + 1) / 2;  // bound on the row-pair grids, whatever the launch shape
   long long gmax = std::max<long long>(kRedBlocks, xgrid);
-  gmax = std::max<long long>(gmax, std::max(p->mrhs.grid, std::max(p->mcor.grid, std::max(p->mres.grid, p->mrs.grid))));
+  for (const auto* c : {&p->mrhs, &p->mcor, &p->mres, &p->mrs}) gmax = std::max<long long>(gmax, c->m.nrec);
   p->pstride = 4 * gmax;
   return true;
 }
@@ -447,12 +441,6 @@ void free_plan(ppe_plan_s* p) {
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   delete p;
-}
-
-// LDS of a marching kernel holding `fields` row arrays (at least the block's
-// reduction scratch, which reuses the same memory after the march)
-size_t march_lds(const ppe_plan_s::MarchCfg& c, int fields) {
-  return (size_t)std::max(fields * c.tslots, c.nt) * 8;
 }
 
 template <typename TS>
@@ -661,10 +649,10 @@ ppe_status_t solve_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb) 
   const double tol = mixed ? p->d.tol : 0.0;
   rho_min_pass(p, tab, inst0, nb);
   PPE_TIMED(p, "k_rhs",
-            PPE_MARCH_SWITCH(p->mrhs, (k_rhs<TS, true, NT><<<dim3(p->mrhs.grid, 1, nb), NT, march_lds(p->mrhs, 4),
+            PPE_MARCH_SWITCH(p->mrhs, (k_rhs<TS, true, NT><<<dim3(p->mrhs.grid, 1, nb), NT, march_lds(p->mrhs, 4, 2),
                                                               p->stream>>>(tab, g, p->mrhs.m, W))));
   // (the sums of the kernel before a forward row transform are reduced by its block 0)
-  ppe_status_t st = launch_r2c<TS>(p, tab, W, nb, p->b64, false, 0, FinishArgs{p->mrhs.grid, FIN_RHS, tol, nullptr, 0});
+  ppe_status_t st = launch_r2c<TS>(p, tab, W, nb, p->b64, false, 0, FinishArgs{p->mrhs.m.nrec, FIN_RHS, tol, nullptr, 0});
   if (st == PPE_OK) st = launch_chain<TS>(p, W, nb, 0);
   if (st == PPE_OK) st = launch_c2r<TS>(p, tab, W, nb, 0, 0);
   if (st != PPE_OK) return st;
@@ -674,9 +662,9 @@ ppe_status_t solve_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb) 
     TS* rs = reinterpret_cast<TS*>(p->r64);
     for (int it = 0; it < p->d.max_refine; ++it) {
       PPE_TIMED(p, "k_resid",
-                PPE_MARCH_SWITCH(p->mrs, (k_resid<TS, NT><<<dim3(p->mrs.grid, 1, nb), NT, march_lds(p->mrs, 2), p->stream>>>(
+                PPE_MARCH_SWITCH(p->mrs, (k_resid<TS, NT><<<dim3(p->mrs.grid, 1, nb), NT, march_lds(p->mrs, 2, 2), p->stream>>>(
                                                 tab, g, p->mrs.m, W, rs))));
-      st = launch_r2c<TS>(p, tab, W, nb, rs, true, 1, FinishArgs{p->mrs.grid, FIN_RESID, 0.0, nullptr, 0});
+      st = launch_r2c<TS>(p, tab, W, nb, rs, true, 1, FinishArgs{p->mrs.m.nrec, FIN_RESID, 0.0, nullptr, 0});
       if (st == PPE_OK) st = launch_chain<TS>(p, W, nb, 1);
       if (st == PPE_OK) st = launch_c2r<TS>(p, tab, W, nb, 1, 1);
       if (st != PPE_OK) return st;
@@ -697,9 +685,9 @@ ppe_status_t varcoef_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb
   rho_min_pass(p, tab, inst0, nb);
   PPE_TIMED(p, "k_rhs",
             PPE_MARCH_SWITCH(p->mrhs, (k_rhs<TS, false, NT><<<dim3(p->mrhs.grid, 1, nb), NT,
-                                                               march_lds(p->mrhs, 0), p->stream>>>(tab, g,
+                                                               march_lds(p->mrhs, 0, 2), p->stream>>>(tab, g,
                                                                                                    p->mrhs.m, W))));
-  finish(p, tab, inst0, nb, p->mrhs.grid, FIN_RHS, 0, tol);
+  finish(p, tab, inst0, nb, p->mrhs.m.nrec, FIN_RHS, 0, tol);
   const int hs = max_iters + 1;
   double* h0 = hist ? hist + (size_t)inst0 * hs : nullptr;
   if (h0) {
@@ -729,19 +717,19 @@ ppe_status_t varcoef_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb
     }
     if (it == 0)
       PPE_TIMED(p, "k_resid_var",
-                PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 1, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4), p->stream>>>(
+                PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 1, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4, 2), p->stream>>>(
                                                 tab, g, p->mres.m, W, p->r64, 1))));
     else
       PPE_TIMED(p, "k_resid_var",
-                PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 0, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4), p->stream>>>(
+                PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 0, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4, 2), p->stream>>>(
                                                 tab, g, p->mres.m, W, p->r64, 1))));
     double* const h = h0 ? h0 + it : nullptr;
     if (it == max_iters) {
-      finish(p, tab, inst0, nb, p->mres.grid, FIN_RESID_LAST, 1, 0.0, h, hs);
+      finish(p, tab, inst0, nb, p->mres.m.nrec, FIN_RESID_LAST, 1, 0.0, h, hs);
       break;
     }
     ppe_status_t st =
-        launch_r2c<TS>(p, tab, W, nb, p->r64, false, 1, FinishArgs{p->mres.grid, FIN_RESID, 0.0, h, hs});
+        launch_r2c<TS>(p, tab, W, nb, p->r64, false, 1, FinishArgs{p->mres.m.nrec, FIN_RESID, 0.0, h, hs});
     if (st == PPE_OK) st = launch_chain<TS>(p, W, nb, 1);
     if (st == PPE_OK) st = launch_c2r<TS>(p, tab, W, nb, 1, 1);
     if (st != PPE_OK) return st;
@@ -759,16 +747,16 @@ ppe_status_t defect_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb,
   Work<TS> W = make_work<TS>(p, inst0);
   PPE_TIMED(p, "k_rhs",
             PPE_MARCH_SWITCH(p->mrhs, (k_rhs<TS, false, NT><<<dim3(p->mrhs.grid, 1, nb), NT,
-                                                               march_lds(p->mrhs, 0), p->stream>>>(tab, p->g,
+                                                               march_lds(p->mrhs, 0, 2), p->stream>>>(tab, p->g,
                                                                                                    p->mrhs.m, W))));
   PPE_TIMED(p, "k_resid_var",
-            PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 2, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4), p->stream>>>(
+            PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 2, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4, 2), p->stream>>>(
                                             tab, p->g, p->mres.m, W, p->r64, 0))));
-  finish(p, tab, inst0, nb, p->mres.grid, FIN_DEFECT, 0, 0.0, out + 2 * (size_t)inst0, 2);
+  finish(p, tab, inst0, nb, p->mres.m.nrec, FIN_DEFECT, 0, 0.0, out + 2 * (size_t)inst0, 2);
   PPE_TIMED(p, "k_resid_var",
-            PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 0, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4), p->stream>>>(
+            PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 0, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4, 2), p->stream>>>(
                                             tab, p->g, p->mres.m, W, p->r64, 0))));
-  finish(p, tab, inst0, nb, p->mres.grid, FIN_DEFECT, 0, 0.0, out + 2 * (size_t)inst0 + 1, 2);
+  finish(p, tab, inst0, nb, p->mres.m.nrec, FIN_DEFECT, 0, 0.0, out + 2 * (size_t)inst0 + 1, 2);
   return hipGetLastError() == hipSuccess ? PPE_OK : PPE_ERR_DEVICE;
 }
 
@@ -1031,9 +1019,9 @@ ppe_status_t ppe_rhs(ppe_plan_t p, const double* rho0, const double* dt, const d
     Work<double> W = make_work<double>(p, i0);
     PPE_TIMED(p, "k_rhs",
               PPE_MARCH_SWITCH(p->mrhs, (k_rhs<double, true, NT><<<dim3(p->mrhs.grid, 1, nb), NT,
-                                                                    march_lds(p->mrhs, 4), p->stream>>>(
+                                                                    march_lds(p->mrhs, 4, 2), p->stream>>>(
                                                tab, g, p->mrhs.m, W))));
-    finish(p, tab, i0, nb, p->mrhs.grid, FIN_RHS, 0);
+    finish(p, tab, i0, nb, p->mrhs.m.nrec, FIN_RHS, 0);
     for (int i = 0; i < nb; ++i)
       if (hipMemcpyAsync(b[i0 + i], p->b64 + (size_t)(i0 + i) * g.npts, (size_t)g.npts * sizeof(double),
                          hipMemcpyDeviceToDevice, p->stream) != hipSuccess)
@@ -1150,7 +1138,7 @@ ppe_status_t ppe_correct(ppe_plan_t p, const double* rho0, const double* dt, con
     }
     PPE_TIMED(p, "k_correct",
               PPE_MARCH_SWITCH(p->mcor, (k_correct<NT><<<dim3(p->mcor.grid, 1, nb), NT,
-                                                            march_lds(p->mcor, 6), p->stream>>>(
+                                                            march_lds(p->mcor, 6, 4), p->stream>>>(
                                                tab, g, p->mcor.m, p->partial, p->pstride, i0, p->scal, tol))));
   }
   return hipGetLastError() == hipSuccess ? PPE_OK : PPE_ERR_DEVICE;

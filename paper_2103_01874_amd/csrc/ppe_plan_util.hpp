@@ -1,6 +1,7 @@
 // ppe_plan_util.hpp -- host-side FFT factorisation and twiddle tables.
 #pragma once
 
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -85,6 +86,42 @@ inline std::vector<double> twiddles(int n) {
     }
   }
   return w;
+}
+
+// ---------------------------------------------------------------------------
+// Planes per block of a marching kernel whose instance has `ntile` tiles a
+// plane, and planes per record of its partial sums.
+//
+// kc, the planes a block marches, follows the instances of a launch: a block
+// pays about 0.7 of a plane for the planes at its ends, and a grid of a few
+// blocks per CU should load the CUs evenly, with at least two on each for their
+// loads to overlap (64x64x64 x 8 k_correct 48 -> 40 us, k_resid 16.3 -> 14.1,
+// 128x512x96 k_correct 121 -> 111 against 2048 blocks an instance).
+//
+// kr, the planes of a record, follows the grid alone -- it is the kc of a single
+// instance -- and kc is a multiple of it: an instance's sums are split in the
+// same way, and so round in the same way, whatever shares its launch.
+// ---------------------------------------------------------------------------
+struct MarchChunks {
+  int kr, kc;
+};
+inline MarchChunks march_chunks(int ntile, int nz, int nb, int max_planes) {
+  const auto best_kc = [&](int instances, int kr) {
+    int kc = 0;
+    double best = 0.0;
+    for (int nkc = (nz + max_planes - 1) / max_planes; nkc <= std::max(1, nz / 2); ++nkc) {
+      const int even = (nz + nkc - 1) / nkc, k = (even + kr - 1) / kr * kr;
+      const double per_cu = (double)ntile * instances * ((nz + k - 1) / k) / 256.0;
+      const double score = per_cu / std::ceil(per_cu) * std::min(1.0, per_cu / 2.0) * even / (k + 0.7);
+      if (k <= std::max(max_planes, kr) && score > best * 1.001) {
+        best = score;
+        kc = k;
+      }
+    }
+    return kc > 0 ? kc : std::max(kr, std::min(nz, max_planes));
+  };
+  const int kr = best_kc(1, 1);
+  return {kr, nb > 1 ? best_kc(nb, kr) : kr};
 }
 
 }  // namespace

@@ -242,3 +242,22 @@ def test_mixed_radix_plans_match_numpy(hc, n):
             assert fn(n, d, _p(xin), _p(out)) == 0
             err.append(float(np.sqrt(((out[0::2] - re) ** 2 + (out[1::2] - im) ** 2).sum() / (re ** 2 + im ** 2).sum())))
         assert err[0] <= err[1] + 2.3e-16, err
+
+
+@pytest.mark.parametrize("max_planes", [16, 32])
+def test_march_records_do_not_depend_on_the_group(hc, max_planes):
+    """Planes per record follow the grid alone; planes per block are whole
+    records and at most max_planes, and every plane is in one block."""
+    f = hc.hc_march_chunks
+    f.argtypes = [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int)] * 2
+    kr, kc = ctypes.c_int(), ctypes.c_int()
+    for ntile in (1, 2, 5, 16, 26, 64, 128, 256, 1000):
+        for nz in (1, 2, 3, 5, 16, 24, 27, 50, 64, 96, 162, 512, 2048):
+            records = set()
+            for nb in range(1, 17):
+                f(ntile, nz, nb, max_planes, ctypes.byref(kr), ctypes.byref(kc))
+                records.add(kr.value)
+                assert kc.value % kr.value == 0 and 1 <= kc.value <= max_planes, (ntile, nz, nb)
+                if nb == 1:
+                    assert kc.value == kr.value
+            assert len(records) == 1, (ntile, nz)
