@@ -44,7 +44,7 @@ enum ScalarSlot {
   SC_ITERS,       // refinement sweeps run
   SC_RHO0_BITS,   // min(rho) accumulator (uint64 bits of a positive double)
   SC_TOL,         // tol
-  SC_SKIP,        // SC_CONV as k_r2c may read it (its block 0 sets SC_CONV): set by k_c2r
+  SC_SKIP,        // SC_CONV as k_r2c may read it (its block 0 sets SC_CONV): set by k_c2r, k_finish
   SC_BLOCKS,      // blocks of the running k_correct that are done (uint32; 0 between launches)
 };
 

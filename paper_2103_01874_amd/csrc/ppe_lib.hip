@@ -664,7 +664,17 @@ ppe_status_t solve_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb) 
       PPE_TIMED(p, "k_resid",
                 PPE_MARCH_SWITCH(p->mrs, (k_resid<TS, NT><<<dim3(p->mrs.grid, 1, nb), NT, march_lds(p->mrs, 2, 2), p->stream>>>(
                                                 tab, g, p->mrs.m, W, rs))));
-      st = launch_r2c<TS>(p, tab, W, nb, rs, true, 1, FinishArgs{p->mrs.m.nrec, FIN_RESID, 0.0, nullptr, 0});
+      // The first solve rarely meets tol: its residual is reduced inside the
+      // row transform.  Later sweeps usually find it met, and the row transform
+      // that finds it runs for nothing: where it costs more than a launch, the
+      // stop test comes ahead of it (max_refine = 2, one sweep needed:
+      // 512x256x512 3900 -> 3763 us, 256x128x256 559 -> 545, 128x128x128 211 ->
+      // 206; 64x64x64 108 -> 110).  By the grid, not the launch: the two ways
+      // add the records up in different orders.
+      const bool ahead = it > 0 && p->d.tol > 0.0 && g.npts >= (1 << 21);
+      if (ahead) finish(p, tab, inst0, nb, p->mrs.m.nrec, FIN_RESID, 1);
+      st = launch_r2c<TS>(p, tab, W, nb, rs, true, 1,
+                          FinishArgs{ahead ? 0 : p->mrs.m.nrec, FIN_RESID, 0.0, nullptr, 0});
       if (st == PPE_OK) st = launch_chain<TS>(p, W, nb, 1);
       if (st == PPE_OK) st = launch_c2r<TS>(p, tab, W, nb, 1, 1);
       if (st != PPE_OK) return st;
@@ -728,6 +738,10 @@ ppe_status_t varcoef_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb
       finish(p, tab, inst0, nb, p->mres.m.nrec, FIN_RESID_LAST, 1, 0.0, h, hs);
       break;
     }
+    // (reduced inside the row transform on every grid: the transform that finds
+    // tol met runs for nothing once a solve, a launch ahead of it would cost
+    // 8-10 us every sweep; 512x256x512 to 1e-6 in 5 sweeps 9.0 ms either way,
+    // in 26 sweeps 40.1 against 40.4)
     ppe_status_t st =
         launch_r2c<TS>(p, tab, W, nb, p->r64, false, 1, FinishArgs{p->mres.m.nrec, FIN_RESID, 0.0, h, hs});
     if (st == PPE_OK) st = launch_chain<TS>(p, W, nb, 1);
