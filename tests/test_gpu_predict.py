@@ -279,3 +279,41 @@ def test_one_march_for_the_three_components(shape, ybc, monkeypatch):
         for name, a, b in zip("uvw", fused, per_face):
             d = np.abs(a - b).max()
             assert d <= 4 * np.finfo(np.float64).eps * np.abs(b).max(), (name, d)
+
+
+@pytest.mark.parametrize("ybc", [0, 1])
+@pytest.mark.parametrize("shape", TILED)
+def test_tiles_with_separate_viscous_velocity(shape, ybc, monkeypatch):
+    """The one-slab tiles (launches whose viscous velocity has arrays of its
+    own) at every tile edge: one and two planes, planes and rows that do not
+    fill a tile, several tiles; against the oracle and the per-face kernels."""
+    g = O.Grid(*shape, 1.1, 0.8, 1.3, ybc=ybc)
+    r = random_inputs(g, 1100 + sum(shape) + ybc)
+    rng = np.random.default_rng(sum(shape))
+    for k, n, s in (("uv", "u", g.shape), ("vv", "v", g.vshape), ("wv", "w", g.shape)):
+        r[k] = r[n] + 0.1 * rng.standard_normal(s)
+    (tiled,) = gpu_predict(g, [r])
+    check(g, r, tiled, f"separate {shape} ybc={ybc}")
+    monkeypatch.setenv("PPE_TUNE_PREDICT_GLOBAL", "1")
+    (per_face,) = gpu_predict(g, [r])
+    for name, a, b in zip("uvw", tiled, per_face):
+        d = np.abs(a - b).max()
+        assert d <= 4 * np.finfo(np.float64).eps * np.abs(b).max(), (name, d)
+
+
+@pytest.mark.parametrize("ybc", [0, 1])
+@pytest.mark.parametrize("shape", [(64, 13, 12), (72, 7, 24), (128, 33, 18), (192, 7, 3), (16, 8, 48)])
+def test_one_march_however_it_is_cut(shape, ybc, monkeypatch):
+    """The planes a block marches follow the launch's size: any cut, alone or
+    two and five instances a launch, gives the same fields bit for bit."""
+    g = O.Grid(*shape, 1.1, 0.8, 1.3, ybc=ybc)
+    recs = [random_inputs(g, 1200 + 3 * sum(shape) + s + ybc) for s in range(5)]
+    alone = [gpu_predict(g, [r])[0] for r in recs]
+    check(g, recs[0], alone[0], f"alone {shape} ybc={ybc}")
+    for n in (2, 5):
+        for got, want in zip(gpu_predict(g, recs[:n]), alone):
+            assert all(np.array_equal(a, b) for a, b in zip(got, want)), n
+    for run in (1, 2, 5, shape[2]):
+        monkeypatch.setenv("PPE_TUNE_PREDICT_RUN", str(run))
+        for got, want in zip(gpu_predict(g, recs[:2]), alone):
+            assert all(np.array_equal(a, b) for a, b in zip(got, want)), run
