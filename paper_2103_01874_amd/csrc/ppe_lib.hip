@@ -1400,6 +1400,59 @@ PredFuse predict_shape(const Geom& g, int nb) {
   m.run = std::max(1, T / 8);  // an XCD takes a band of tile rows of every chunk
   return m;
 }
+
+// The predictor of nb instances, all with (alias) or all without the advected
+// velocity in the viscous term.
+void predict_launch(ppe_plan_s* p, const PredTable& tab, int nb, bool alias) {
+  const Geom& g = p->g;
+  const unsigned blocks = (unsigned)((g.npts + 255) / 256);
+  // LDS tiles need whole 64-column x tiles; PPE_TUNE_PREDICT_GLOBAL=1 keeps
+  // the one-thread-per-face kernels (the same arithmetic on the same values)
+  const bool tiled = tune_env("PPE_TUNE_PREDICT_GLOBAL") == 0 && g.nx % kPredTX == 0;
+  // any row length: against the one-thread-per-face kernels a 16x64x16 flow
+  // step takes 75 instead of 82 us, 96x64x96 x 4 317 instead of 603
+  if (alias && tune_env("PPE_TUNE_PREDICT_GLOBAL") == 0) {
+    const PredFuse m = predict_shape(g, nb);
+    const unsigned grid = 8u * m.run * ((((unsigned)m.nt + m.run - 1) / m.run + 7u) / 8u);
+    PPE_TIMED(p, "k_predict", {
+      k_predict_fused<<<dim3(grid, 1, nb), 64 * kFuseTJ, 0, p->stream>>>(tab, g, m);
+      if (g.ybc == 1) {  // the outflow top face of v
+        const unsigned tblocks = (unsigned)(((long long)g.nx * g.nz + 255) / 256);
+        k_predict_vtop<<<dim3(tblocks, 1, nb), 256, 0, p->stream>>>(tab, g);
+      }
+    });
+    return;
+  }
+  if (tiled) {
+    const unsigned ntx = (unsigned)(g.nx / kPredTX);
+    const dim3 gy(ntx * (unsigned)((g.ny + kPredTR - 1) / kPredTR), (unsigned)g.nz, nb);
+    const dim3 gz(ntx * (unsigned)((g.nz + kPredTR - 1) / kPredTR), (unsigned)g.ny, nb);
+    constexpr int nt = kPredTX * kPredTR;
+    PPE_TIMED(p, "k_predict_u", {
+      k_predict_tile<0><<<gy, nt, 0, p->stream>>>(tab, g);
+    });
+    PPE_TIMED(p, "k_predict_v", {
+      k_predict_tile<1><<<gy, nt, 0, p->stream>>>(tab, g);
+      if (g.ybc == 1) {  // the outflow top face
+        const unsigned tblocks = (unsigned)(((long long)g.nx * g.nz + 255) / 256);
+        k_predict_vtop<<<dim3(tblocks, 1, nb), 256, 0, p->stream>>>(tab, g);
+      }
+    });
+    PPE_TIMED(p, "k_predict_w", {
+      k_predict_tile<2><<<gz, nt, 0, p->stream>>>(tab, g);
+    });
+    return;
+  }
+  PPE_TIMED(p, "k_predict_u", (k_predict<0><<<dim3(blocks, 1, nb), 256, 0, p->stream>>>(tab, g)));
+  PPE_TIMED(p, "k_predict_v", {
+    k_predict<1><<<dim3(blocks, 1, nb), 256, 0, p->stream>>>(tab, g);
+    if (g.ybc == 1) {  // the outflow top face
+      const unsigned tblocks = (unsigned)(((long long)g.nx * g.nz + 255) / 256);
+      k_predict_vtop<<<dim3(tblocks, 1, nb), 256, 0, p->stream>>>(tab, g);
+    }
+  });
+  PPE_TIMED(p, "k_predict_w", (k_predict<2><<<dim3(blocks, 1, nb), 256, 0, p->stream>>>(tab, g)));
+}
 }  // namespace
 
 ppe_status_t ppe_predict(ppe_plan_t p, const ppe_predict_t* in, double* const* up, double* const* vp,
@@ -1415,18 +1468,17 @@ ppe_status_t ppe_predict(ppe_plan_t p, const ppe_predict_t* in, double* const* u
     if (!(q.dt > 0) || !std::isfinite(q.dt) || !(q.rho_mean > 0) || !std::isfinite(q.rho_mean)) return PPE_ERR_ARG;
   }
   if (hipSetDevice(p->device) != hipSuccess) return PPE_ERR_DEVICE;
-  const Geom& g = p->g;
-  const unsigned blocks = (unsigned)((g.npts + 255) / 256);
-  // LDS tiles need whole 64-column x tiles; PPE_TUNE_PREDICT_GLOBAL=1 keeps
-  // the one-thread-per-face kernels (the same arithmetic on the same values)
-  const bool tiled = tune_env("PPE_TUNE_PREDICT_GLOBAL") == 0 && g.nx % kPredTX == 0;
   for (int i0 = 0; i0 < B; i0 += kMaxLaunch) {
     const int nb = std::min(kMaxLaunch, B - i0);
-    PredTable tab;
-    std::memset(&tab, 0, sizeof(tab));
+    // the instances whose viscous-term velocity is the advected one ([0]) and
+    // the others: an instance takes the kernels it would take alone
+    PredTable tab[2];
+    int n[2] = {0, 0};
+    std::memset(tab, 0, sizeof(tab));
     for (int i = 0; i < nb; ++i) {
       const ppe_predict_t& q = in[i0 + i];
-      PredPtrs& t = tab.in[i];
+      const bool own = (q.uv && q.uv != q.u) || (q.vv && q.vv != q.v) || (q.wv && q.wv != q.w);
+      PredPtrs& t = tab[own].in[n[own]++];
       t.u = q.u;
       t.v = q.v;
       t.w = q.w;
@@ -1448,55 +1500,8 @@ ppe_status_t ppe_predict(ppe_plan_t p, const ppe_predict_t* in, double* const* u
       t.rho_mean = q.rho_mean;
       t.dt = q.dt;
     }
-    // the viscous-term velocity is the advected one in every instance
-    bool alias = true;
-    for (int i = 0; i < nb; ++i) {
-      const PredPtrs& t = tab.in[i];
-      alias = alias && t.uv == t.u && t.vv == t.v && t.wv == t.w;
-    }
-    // any row length: against the one-thread-per-face kernels a 16x64x16 flow
-    // step takes 75 instead of 82 us, 96x64x96 x 4 317 instead of 603
-    if (alias && tune_env("PPE_TUNE_PREDICT_GLOBAL") == 0) {
-      const PredFuse m = predict_shape(g, nb);
-      const unsigned grid = 8u * m.run * ((((unsigned)m.nt + m.run - 1) / m.run + 7u) / 8u);
-      PPE_TIMED(p, "k_predict", {
-        k_predict_fused<<<dim3(grid, 1, nb), 64 * kFuseTJ, 0, p->stream>>>(tab, g, m);
-        if (g.ybc == 1) {  // the outflow top face of v
-          const unsigned tblocks = (unsigned)(((long long)g.nx * g.nz + 255) / 256);
-          k_predict_vtop<<<dim3(tblocks, 1, nb), 256, 0, p->stream>>>(tab, g);
-        }
-      });
-      continue;
-    }
-    if (tiled) {
-      const unsigned ntx = (unsigned)(g.nx / kPredTX);
-      const dim3 gy(ntx * (unsigned)((g.ny + kPredTR - 1) / kPredTR), (unsigned)g.nz, nb);
-      const dim3 gz(ntx * (unsigned)((g.nz + kPredTR - 1) / kPredTR), (unsigned)g.ny, nb);
-      constexpr int nt = kPredTX * kPredTR;
-      PPE_TIMED(p, "k_predict_u", {
-        k_predict_tile<0><<<gy, nt, 0, p->stream>>>(tab, g);
-      });
-      PPE_TIMED(p, "k_predict_v", {
-        k_predict_tile<1><<<gy, nt, 0, p->stream>>>(tab, g);
-        if (g.ybc == 1) {  // the outflow top face
-          const unsigned tblocks = (unsigned)(((long long)g.nx * g.nz + 255) / 256);
-          k_predict_vtop<<<dim3(tblocks, 1, nb), 256, 0, p->stream>>>(tab, g);
-        }
-      });
-      PPE_TIMED(p, "k_predict_w", {
-        k_predict_tile<2><<<gz, nt, 0, p->stream>>>(tab, g);
-      });
-      continue;
-    }
-    PPE_TIMED(p, "k_predict_u", (k_predict<0><<<dim3(blocks, 1, nb), 256, 0, p->stream>>>(tab, g)));
-    PPE_TIMED(p, "k_predict_v", {
-      k_predict<1><<<dim3(blocks, 1, nb), 256, 0, p->stream>>>(tab, g);
-      if (g.ybc == 1) {  // the outflow top face
-        const unsigned tblocks = (unsigned)(((long long)g.nx * g.nz + 255) / 256);
-        k_predict_vtop<<<dim3(tblocks, 1, nb), 256, 0, p->stream>>>(tab, g);
-      }
-    });
-    PPE_TIMED(p, "k_predict_w", (k_predict<2><<<dim3(blocks, 1, nb), 256, 0, p->stream>>>(tab, g)));
+    if (n[0] > 0) predict_launch(p, tab[0], n[0], true);
+    if (n[1] > 0) predict_launch(p, tab[1], n[1], false);
   }
   return hipGetLastError() == hipSuccess ? PPE_OK : PPE_ERR_DEVICE;
 }

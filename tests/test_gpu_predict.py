@@ -317,3 +317,25 @@ def test_one_march_however_it_is_cut(shape, ybc, monkeypatch):
         monkeypatch.setenv("PPE_TUNE_PREDICT_RUN", str(run))
         for got, want in zip(gpu_predict(g, recs[:2]), alone):
             assert all(np.array_equal(a, b) for a, b in zip(got, want)), run
+
+
+@pytest.mark.parametrize("shape,ybc", [((64, 9, 12), 1), ((128, 13, 6), 0), ((24, 8, 18), 0)])
+def test_group_of_both_viscous_forms_equals_alone(shape, ybc):
+    """Instances with and without a viscous velocity of their own in one
+    launch: each takes the kernels it takes alone, so its fields are the same
+    bit for bit."""
+    g = O.Grid(*shape, 1.0, 1.0, 1.0, ybc=ybc)
+    rng = np.random.default_rng(43)
+    recs = []
+    for s in range(4):
+        r = random_inputs(g, 1300 + s)
+        if s in (1, 2):
+            r["uv"] = r["u"] + 0.1 * rng.standard_normal(g.shape)
+            r["vv"] = r["v"] + 0.1 * rng.standard_normal(g.vshape)
+            r["wv"] = r["w"] + 0.1 * rng.standard_normal(g.shape)
+        recs.append(r)
+    for r, got in zip(recs, gpu_predict(g, recs)):
+        check(g, r, got, f"both forms {shape} ybc={ybc}")
+        (alone,) = gpu_predict(g, [r])
+        for a, b in zip(alone, got):
+            assert np.array_equal(a, b)
