@@ -72,6 +72,7 @@ struct ppe_plan_s {
   int spec_chunks = 1;   // kx chunks the spectral chain runs in (see launch_chain)
   int src_pt = 8;        // units per thread of k_source (2, 4 or 8)
   int src_vec = 2;       // cells per unit of k_source (1, or 2 when aligned)
+  PredFuse pred[kMaxLaunch + 1];  // k_predict_fused's shape by instances per launch (kc = 0: not planned yet)
   size_t lds_x = 0, lds_z = 0, lds_t = 0;
   // z-marching stencil tiles, one shape per kernel
   struct MarchCfg {
@@ -1374,30 +1375,34 @@ ppe_status_t ppe_ring_destroy(ppe_ring_t r) {
 }
 
 namespace {
+// m's march cut into chunks of kc planes.
+void predict_cut(const Geom& g, PredFuse& m, int kc) {
+  m.kc = kc;
+  m.nkc = (g.nz + kc - 1) / kc;
+  m.nt = m.ntx * m.ntj * m.nkc;
+  m.run = std::max(1, m.ntx * m.ntj / 8);  // an XCD takes a band of tile rows of every chunk
+}
+
 // Tiles and planes per block of k_predict_fused: one block runs on a CU at a
 // time, and pays about two planes for the ends of its march.
 PredFuse predict_shape(const Geom& g, int nb) {
-  PredFuse m;
+  PredFuse m{};
   m.ntx = (g.nx + 63) / 64;
   m.w = (g.nx + m.ntx - 1) / m.ntx;
   m.ntx = (g.nx + m.w - 1) / m.w;
   m.ntj = (g.ny + kFuseTJ - 1) / kFuseTJ;
-  const int T = m.ntx * m.ntj;
-  m.kc = g.nz;
+  int best_kc = g.nz;
   double best = 0.0;
   for (int nkc = 1; nkc <= g.nz; ++nkc) {
     const int kc = (g.nz + nkc - 1) / nkc;
-    const double rounds = (double)T * nb * ((g.nz + kc - 1) / kc) / 256.0;
+    const double rounds = (double)m.ntx * m.ntj * nb * ((g.nz + kc - 1) / kc) / 256.0;
     const double score = rounds / std::ceil(rounds) * kc / (kc + 2.0);
     if (score > best * 1.001) {
       best = score;
-      m.kc = kc;
+      best_kc = kc;
     }
   }
-  if (tune_env("PPE_TUNE_PREDICT_RUN") > 0) m.kc = std::min(g.nz, tune_env("PPE_TUNE_PREDICT_RUN"));
-  m.nkc = (g.nz + m.kc - 1) / m.kc;
-  m.nt = T * m.nkc;
-  m.run = std::max(1, T / 8);  // an XCD takes a band of tile rows of every chunk
+  predict_cut(g, m, best_kc);
   return m;
 }
 
@@ -1406,13 +1411,15 @@ PredFuse predict_shape(const Geom& g, int nb) {
 void predict_launch(ppe_plan_s* p, const PredTable& tab, int nb, bool alias) {
   const Geom& g = p->g;
   const unsigned blocks = (unsigned)((g.npts + 255) / 256);
-  // LDS tiles need whole 64-column x tiles; PPE_TUNE_PREDICT_GLOBAL=1 keeps
-  // the one-thread-per-face kernels (the same arithmetic on the same values)
-  const bool tiled = tune_env("PPE_TUNE_PREDICT_GLOBAL") == 0 && g.nx % kPredTX == 0;
+  // PPE_TUNE_PREDICT_GLOBAL=1: the one-thread-per-face kernels
+  const bool global = tune_env("PPE_TUNE_PREDICT_GLOBAL") != 0;
   // any row length: against the one-thread-per-face kernels a 16x64x16 flow
   // step takes 75 instead of 82 us, 96x64x96 x 4 317 instead of 603
-  if (alias && tune_env("PPE_TUNE_PREDICT_GLOBAL") == 0) {
-    const PredFuse m = predict_shape(g, nb);
+  if (alias && !global) {
+    PredFuse m = p->pred[nb];
+    if (m.kc == 0) p->pred[nb] = m = predict_shape(g, nb);
+    const int run = tune_env("PPE_TUNE_PREDICT_RUN");
+    if (run > 0) predict_cut(g, m, std::min(g.nz, run));
     const unsigned grid = 8u * m.run * ((((unsigned)m.nt + m.run - 1) / m.run + 7u) / 8u);
     PPE_TIMED(p, "k_predict", {
       k_predict_fused<<<dim3(grid, 1, nb), 64 * kFuseTJ, 0, p->stream>>>(tab, g, m);
@@ -1423,7 +1430,7 @@ void predict_launch(ppe_plan_s* p, const PredTable& tab, int nb, bool alias) {
     });
     return;
   }
-  if (tiled) {
+  if (!global && g.nx % kPredTX == 0) {  // (the tiles need whole 64-column x tiles)
     const unsigned ntx = (unsigned)(g.nx / kPredTX);
     const dim3 gy(ntx * (unsigned)((g.ny + kPredTR - 1) / kPredTR), (unsigned)g.nz, nb);
     const dim3 gz(ntx * (unsigned)((g.nz + kPredTR - 1) / kPredTR), (unsigned)g.ny, nb);
