@@ -60,7 +60,7 @@ def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     units = [("ppe_lib.hip", "ppe_lib.o", ())]
     units += [("ppe_fft.hip", f"ppe_fft_{ts}{grp}.o", (f"-DPPE_FFT_GROUP={grp}", f"-DPPE_FFT_TS={ts}"))
-              for grp in range(4) for ts in ("double", "float")]
+              for grp in range(5) for ts in ("double", "float")]
     with ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as ex:
         objs = [ex.submit(_compile, os.path.join(CSRC, src), os.path.join(OBJ, out), ("-c", *defs), verbose)
                 for src, out, defs in units]

@@ -245,7 +245,18 @@ int hc_fft_mixed(int n, int dir, const double* in, double* out) {
     HC_CT(324)
     HC_CT(432)
     HC_CT(486)
+    HC_CT(576)
+    HC_CT(648)
+    HC_CT(729)
     HC_CT(768)
+    HC_CT(864)
+    HC_CT(972)
+    HC_CT(1152)
+    HC_CT(1296)
+    HC_CT(1458)
+    HC_CT(1536)
+    HC_CT(1728)
+    HC_CT(1944)
     default:
       return -1;
   }

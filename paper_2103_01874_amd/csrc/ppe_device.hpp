@@ -102,10 +102,10 @@ struct FftDev {
 // Compile-time plan of length N.  Stage counts, radices, sub-transform lengths
 // and twiddle steps are constants, so the stage loop unrolls, the radix
 // dispatch folds away and j / ns, j mod ns become shifts and multiplications.
-// Only the twiddle table is a run-time value.  Powers of two and three times a
-// power of two take the host's factors (radix-8 stages and a last radix 4 or
-// 2; a radix-3 stage, then radix 4 and 2); the other products of twos and
-// threes take the radices of kMixedPlans.
+// Only the twiddle table is a run-time value.  Every length of 16 and more that
+// the library accepts has one: powers of two and 96, 192, 384 take the host's
+// factors (radix-8 stages and a last radix 4 or 2; a radix-3 stage, then radix
+// 4 and 2), the other products of twos and threes the radices of kMixedPlans.
 struct StageTab {
   int radix[kMaxStages];
   int ns[kMaxStages];
@@ -156,18 +156,24 @@ constexpr bool is_pow2_c(int n) { return n >= 1 && (n & (n - 1)) == 0; }
 // Two or three stages of radix 6, 9, 12 or 18 instead of the run-time plans'
 // four to six of radix 2, 3 and 4: a stage costs a pass through LDS and two
 // barriers.  E, the elements per thread, is the lcm of the radices and at most
-// 18 (36 doubles of registers).  Against the run-time plans: k_fft_z 36 -> 15 us
-// and k_r2c 25 -> 17.5 at 162x100x216, 29 -> 17 and 32 -> 27.5 at 486x60x144,
-// k_r2c 42 -> 27 at 72x200x81 x 5, every one of 10 -> 7 us at 54x37x48.
+// 18 (36 doubles of registers); lengths with a single three keep radix 4 after
+// their 12.  Against the run-time plans every length is faster: k_fft_z 36 -> 15
+// us and k_r2c 25 -> 17.5 at 162x100x216, 29 -> 17 and 32 -> 27.5 at 486x60x144,
+// k_r2c 42 -> 27 at 72x200x81 x 5, every one of 10 -> 7 us at 54x37x48; of the
+// long ones (96 x 48 rows or columns) forward z between 24 -> 21 at 729 and
+// 118 -> 55 at 1944, k_c2r between 22 -> 17 at 729 and 95 -> 42 at 1944.
 struct MixedPlan {
-  int n, e, nst, radix[4];
+  int n, e, nst, radix[5];
 };
 constexpr MixedPlan kMixedPlans[] = {
     {18, 6, 2, {6, 3}},       {24, 12, 2, {12, 2}},      {27, 9, 2, {9, 3}},       {36, 6, 2, {6, 6}},
     {48, 12, 2, {12, 4}},     {54, 18, 2, {9, 6}},       {72, 12, 2, {12, 6}},     {81, 9, 2, {9, 9}},
     {108, 18, 2, {18, 6}},    {144, 12, 2, {12, 12}},    {162, 18, 2, {18, 9}},    {216, 6, 3, {6, 6, 6}},
     {243, 9, 3, {9, 9, 3}},   {288, 12, 3, {12, 12, 2}}, {324, 18, 2, {18, 18}},   {432, 12, 3, {12, 12, 3}},
-    {486, 18, 3, {18, 9, 3}}, {768, 12, 4, {12, 4, 4, 4}}};
+    {486, 18, 3, {18, 9, 3}}, {576, 12, 3, {12, 12, 4}}, {648, 18, 3, {18, 18, 2}}, {729, 9, 3, {9, 9, 9}},
+    {768, 12, 4, {12, 4, 4, 4}},   {864, 12, 3, {12, 12, 6}},     {972, 18, 3, {18, 9, 6}},
+    {1152, 12, 4, {12, 12, 4, 2}}, {1296, 12, 4, {12, 12, 3, 3}}, {1458, 18, 3, {18, 9, 9}},
+    {1536, 12, 5, {12, 4, 4, 4, 2}}, {1728, 12, 3, {12, 12, 12}}, {1944, 18, 3, {18, 18, 6}}};
 constexpr MixedPlan mixed_plan(int n) {
   for (const MixedPlan& p : kMixedPlans)
     if (p.n == n) return p;

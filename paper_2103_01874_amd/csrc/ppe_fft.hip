@@ -31,8 +31,10 @@ bool with_plan(const FftDev& f, Call call) {
     PPE_FFT_GROUP_1(PPE_FFT_CT)
 #elif PPE_FFT_GROUP == 2
     PPE_FFT_GROUP_2(PPE_FFT_CT)
-#else
+#elif PPE_FFT_GROUP == 3
     PPE_FFT_GROUP_3(PPE_FFT_CT)
+#else
+    PPE_FFT_GROUP_4(PPE_FFT_CT)
 #endif
     default: return false;
   }
@@ -101,8 +103,10 @@ bool FftGroup<GROUP, TS>::allow_lds(int bytes) {
   PPE_FFT_GROUP_1(PPE_FFT_ALLOW)
 #elif PPE_FFT_GROUP == 2
   PPE_FFT_GROUP_2(PPE_FFT_ALLOW)
-#else
+#elif PPE_FFT_GROUP == 3
   PPE_FFT_GROUP_3(PPE_FFT_ALLOW)
+#else
+  PPE_FFT_GROUP_4(PPE_FFT_ALLOW)
 #endif
 #endif
   return ok;

@@ -485,7 +485,8 @@ Work<TS> make_work(ppe_plan_s* p, int inst0) {
       case 0: { using G = FftGroup<0, TS>; return CALL; }  \
       case 1: { using G = FftGroup<1, TS>; return CALL; }  \
       case 2: { using G = FftGroup<2, TS>; return CALL; }  \
-      default: { using G = FftGroup<3, TS>; return CALL; } \
+      case 3: { using G = FftGroup<3, TS>; return CALL; }  \
+      default: { using G = FftGroup<4, TS>; return CALL; } \
     }                                                      \
   }()
 
@@ -789,7 +790,8 @@ namespace {
 template <typename TS>
 bool allow_big_lds_t(int bytes) {
   return FftGroup<0, TS>::allow_lds(bytes) && FftGroup<1, TS>::allow_lds(bytes) &&
-         FftGroup<2, TS>::allow_lds(bytes) && FftGroup<3, TS>::allow_lds(bytes);
+         FftGroup<2, TS>::allow_lds(bytes) && FftGroup<3, TS>::allow_lds(bytes) &&
+         FftGroup<4, TS>::allow_lds(bytes);
 }
 bool allow_big_lds(int bytes) { return allow_big_lds_t<double>(bytes) && allow_big_lds_t<float>(bytes); }
 

@@ -25,3 +25,12 @@ def test_mixed_radix_lengths(n, precision):
         got, rec = (run_single(pr, precision, 0) if precision == binding.PPE_PREC_FP64
                     else run_single(pr, precision, 3, tol=1e-13))
         PU.check(pr, got, rec, PU.oracle_step(pr), label=f"{shape} ybc={ybc} ")
+
+
+LONG = [576, 648, 729, 864, 972, 1152, 1296, 1458, 1536, 1728, 1944]
+
+
+@pytest.mark.parametrize("precision", [binding.PPE_PREC_FP64, binding.PPE_PREC_MIXED])
+@pytest.mark.parametrize("n", LONG)
+def test_long_mixed_radix_lengths(n, precision):
+    test_mixed_radix_lengths(n, precision)

@@ -261,3 +261,20 @@ def test_march_records_do_not_depend_on_the_group(hc, max_planes):
                 if nb == 1:
                     assert kc.value == kr.value
             assert len(records) == 1, (ntile, nz)
+
+
+# the other lengths of the form 2^a 3^b of 16 and more that are accepted
+LONG = [576, 648, 729, 864, 972, 1152, 1296, 1458, 1536, 1728, 1944]
+
+
+@pytest.mark.parametrize("n", LONG)
+def test_long_mixed_radix_plans_match_numpy(hc, n):
+    test_mixed_radix_plans_match_numpy(hc, n)
+
+
+def test_every_accepted_length_has_a_compile_time_plan(hc):
+    x, out = np.zeros(2 * 2048), np.zeros(2 * 2048)
+    hc.hc_fft_mixed.argtypes = hc.hc_fft.argtypes
+    for n in sorted(2 ** a * 3 ** b for a in range(12) for b in range(7)):
+        if 16 <= n <= 2048:
+            assert hc.hc_fft_mixed(n, -1, _p(x), _p(out)) == 0 or hc.hc_fft_ct(n, -1, _p(x), _p(out)) == 0, n
