@@ -78,7 +78,7 @@ bool FftGroup<GROUP, TS>::fft_z(const FftLaunch& l, const FftDev& f, const Geom&
 }
 
 template <int GROUP, typename TS>
-bool FftGroup<GROUP, TS>::allow_lds(int bytes) {
+bool FftGroup<GROUP, TS>::allow_lds(int bytes, const FftDev* only) {
   const auto allow = [&](auto e, const auto& F) {
     using P = std::decay_t<decltype(F)>;
     constexpr int E = decltype(e)::value;
@@ -88,6 +88,7 @@ bool FftGroup<GROUP, TS>::allow_lds(int bytes) {
       if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return false;
     return true;
   };
+  if (only) return with_plan(*only, allow);
   FftDev f{};
   bool ok = true;
 #if PPE_FFT_GROUP == 0

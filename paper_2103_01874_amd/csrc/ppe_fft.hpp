@@ -45,8 +45,8 @@ struct FftGroup {
                   int mode, int check);
   static bool fft_z(const FftLaunch& l, const FftDev& f, const Geom& g, const Work<TS>& W, int tx, int dir, int check,
                     int kx0, int pair);
-  // dynamic LDS above 64 KiB, for every z kernel of the group
-  static bool allow_lds(int bytes);
+  // dynamic LDS above 64 KiB, for the z kernels of plan `only` (nullptr: of the group)
+  static bool allow_lds(int bytes, const FftDev* only);
 };
 
 // Elements and threads per transform of a length's compile-time plan.

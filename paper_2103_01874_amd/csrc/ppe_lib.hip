@@ -786,14 +786,25 @@ bool ptrs_ok(const void* const* a, int n) {
 }  // namespace
 
 namespace {
-// Dynamic LDS above 64 KiB must be enabled per kernel (all z-FFT variants).
-template <typename TS>
-bool allow_big_lds_t(int bytes) {
-  return FftGroup<0, TS>::allow_lds(bytes) && FftGroup<1, TS>::allow_lds(bytes) &&
-         FftGroup<2, TS>::allow_lds(bytes) && FftGroup<3, TS>::allow_lds(bytes) &&
-         FftGroup<4, TS>::allow_lds(bytes);
+// Dynamic LDS above 64 KiB must be enabled per kernel: a plan does it for its
+// own two z kernels (the first plan of a process 15 ms when all of them were
+// enabled, and so loaded; 2 ms), the shared scratch once for all.  `bytes` is
+// the device's limit, so that no plan lowers another's.
+bool allow_big_lds(const ppe_plan_s* p, int bytes) {
+  const FftDev f = to_dev(p->fz);
+  if (p->d.precision == PPE_PREC_FP64) {
+    using TS = double;
+    return PPE_FFT_DISPATCH(p->fz_ct, G::allow_lds(bytes, &f));
+  }
+  using TS = float;
+  return PPE_FFT_DISPATCH(p->fz_ct, G::allow_lds(bytes, &f));
 }
-bool allow_big_lds(int bytes) { return allow_big_lds_t<double>(bytes) && allow_big_lds_t<float>(bytes); }
+template <typename TS>
+bool allow_big_lds_all(int bytes) {
+  bool ok = true;
+  for (int g = 0; g <= 4; ++g) ok = ok && PPE_FFT_DISPATCH(g, G::allow_lds(bytes, nullptr));
+  return ok;
+}
 
 }  // namespace
 
@@ -822,7 +833,7 @@ void* scratch_on(int dev) {
   if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return nullptr;
   int lds_max = 65536;
   if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return nullptr;
-  if (lds_max > 65536 && !allow_big_lds(lds_max)) return nullptr;
+  if (lds_max > 65536 && !(allow_big_lds_all<double>(lds_max) && allow_big_lds_all<float>(lds_max))) return nullptr;
   g_scratch_ptr[dev] = ptr;
   return ptr;
 }
@@ -890,7 +901,7 @@ ppe_status_t ppe_plan(const ppe_desc_t* desc, void* stream, ppe_plan_t* out) {
     delete p;
     return PPE_ERR_UNSUPPORTED;
   }
-  if (p->lds_z > 65536 && !allow_big_lds((int)p->lds_z)) {
+  if (p->lds_z > 65536 && !allow_big_lds(p, lds_max)) {
     delete p;
     return PPE_ERR_DEVICE;
   }
