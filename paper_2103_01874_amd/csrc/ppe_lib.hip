@@ -331,7 +331,7 @@ bool shape_plan(ppe_plan_s* p, size_t lds_limit = 65536) {
       tune_env("PPE_TUNE_MAX_PLANES_COR") > 0 ? tune_env("PPE_TUNE_MAX_PLANES_COR") : (big_cor ? planes : 32);
   if (!march_shape(d, 64, "PPE_TUNE_TJ_RHS", p->mrhs, nt_rhs, planes) ||
       !march_shape(d, 64, "PPE_TUNE_TJ_COR", p->mcor, nt_cor, planes_cor) ||
-      !march_shape(d, 64, "PPE_TUNE_TJ_RES", p->mres, 512, 16) || !march_shape(d, 64, "PPE_TUNE_TJ_RS", p->mrs, 512, 16))
+      !march_shape(d, 64, "PPE_TUNE_TJ_RES", p->mres, kResThreads, 16) || !march_shape(d, 64, "PPE_TUNE_TJ_RS", p->mrs, kResThreads, 16))
     return false;
   if (march_lds(p->mcor, 6, 4) > 65536) return false;
   // per-instance partial-sum stride: the most records of a reducing kernel
@@ -469,8 +469,8 @@ Work<TS> make_work(ppe_plan_s* p, int inst0) {
   return w;
 }
 
-// Launch CALL with NT the threads per block of launch shape CFG (k_rhs and
-// k_correct: one point per thread).
+// Launch CALL with NT the threads per block of launch shape CFG (k_rhs,
+// k_correct).
 #define PPE_MARCH_SWITCH(CFG, CALL)                     \
   switch ((CFG).nt) {                                   \
     case 256: { constexpr int NT = 256; CALL; } break;  \
@@ -664,8 +664,8 @@ ppe_status_t solve_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb) 
     TS* rs = reinterpret_cast<TS*>(p->r64);
     for (int it = 0; it < p->d.max_refine; ++it) {
       PPE_TIMED(p, "k_resid",
-                PPE_MARCH_SWITCH(p->mrs, (k_resid<TS, NT><<<dim3(p->mrs.grid, 1, nb), NT, march_lds(p->mrs, 2, 2), p->stream>>>(
-                                                tab, g, p->mrs.m, W, rs))));
+                (k_resid<TS><<<dim3(p->mrs.grid, 1, nb), kResThreads, march_lds(p->mrs, 2, 2), p->stream>>>(
+                                                tab, g, p->mrs.m, W, rs)));
       // The first solve rarely meets tol: its residual is reduced inside the
       // row transform.  Later sweeps usually find it met, and the row transform
       // that finds it runs for nothing: where it costs more than a launch, the
@@ -729,12 +729,12 @@ ppe_status_t varcoef_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb
     }
     if (it == 0)
       PPE_TIMED(p, "k_resid_var",
-                PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 1, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4, 2), p->stream>>>(
-                                                tab, g, p->mres.m, W, p->r64, 1))));
+                (k_resid_var<TS, 1><<<dim3(p->mres.grid, 1, nb), kResThreads, march_lds(p->mres, 4, 2), p->stream>>>(
+                                                tab, g, p->mres.m, W, p->r64, 1)));
     else
       PPE_TIMED(p, "k_resid_var",
-                PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 0, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4, 2), p->stream>>>(
-                                                tab, g, p->mres.m, W, p->r64, 1))));
+                (k_resid_var<TS, 0><<<dim3(p->mres.grid, 1, nb), kResThreads, march_lds(p->mres, 4, 2), p->stream>>>(
+                                                tab, g, p->mres.m, W, p->r64, 1)));
     double* const h = h0 ? h0 + it : nullptr;
     if (it == max_iters) {
       finish(p, tab, inst0, nb, p->mres.m.nrec, FIN_RESID_LAST, 1, 0.0, h, hs);
@@ -766,12 +766,12 @@ ppe_status_t defect_typed(ppe_plan_s* p, const PtrTable& tab, int inst0, int nb,
                                                                march_lds(p->mrhs, 0, 2), p->stream>>>(tab, p->g,
                                                                                                    p->mrhs.m, W))));
   PPE_TIMED(p, "k_resid_var",
-            PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 2, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4, 2), p->stream>>>(
-                                            tab, p->g, p->mres.m, W, p->r64, 0))));
+            (k_resid_var<TS, 2><<<dim3(p->mres.grid, 1, nb), kResThreads, march_lds(p->mres, 4, 2), p->stream>>>(
+                                            tab, p->g, p->mres.m, W, p->r64, 0)));
   finish(p, tab, inst0, nb, p->mres.m.nrec, FIN_DEFECT, 0, 0.0, out + 2 * (size_t)inst0, 2);
   PPE_TIMED(p, "k_resid_var",
-            PPE_MARCH_SWITCH(p->mres, (k_resid_var<TS, 0, NT><<<dim3(p->mres.grid, 1, nb), NT, march_lds(p->mres, 4, 2), p->stream>>>(
-                                            tab, p->g, p->mres.m, W, p->r64, 0))));
+            (k_resid_var<TS, 0><<<dim3(p->mres.grid, 1, nb), kResThreads, march_lds(p->mres, 4, 2), p->stream>>>(
+                                            tab, p->g, p->mres.m, W, p->r64, 0)));
   finish(p, tab, inst0, nb, p->mres.m.nrec, FIN_DEFECT, 0, 0.0, out + 2 * (size_t)inst0 + 1, 2);
   return hipGetLastError() == hipSuccess ? PPE_OK : PPE_ERR_DEVICE;
 }
