@@ -304,17 +304,17 @@ bool shape_plan(ppe_plan_s* p, size_t lds_limit = 65536) {
   if (tune_env("PPE_TUNE_SRC_VEC") > 0) p->src_vec = tune_env("PPE_TUNE_SRC_VEC");
   if (p->src_pt != 2 && p->src_pt != 4) p->src_pt = 8;
   if (p->src_vec != 1) p->src_vec = 2;
-  // z-marching stencils: TXT x TJ tiles (TXT a divisor of nx, <= 128), KC planes
-  // per chunk; the tile height per kernel trades halo traffic against registers
-  // k_rhs and k_correct take one point per thread.  512 threads (64 x 8 tiles)
-  // fetch fewer halo rows per interior row than 256 (64 x 4) and win where
-  // those rows no longer stay in L2: k_correct from planes of 64 K cells
-  // (512x256x512: 1107 against 1184 us, 512x128x256: 327 against 345;
-  // 384x192x324: 470 against 463), k_rhs from 16 K cells where the tile rows
-  // are whole wavefronts (256x256x256: 213 against 224; rows of 48 cells leave
-  // threads idle, 96x64x96 x 12: 99 against 88).  A block marches at most 16
-  // planes; 32 on planes of 128 K cells, and in k_correct's small tiles (a
-  // 256x128x256 step 401.6 against 403.5 us: the k_rhs that follows is faster).
+  // z-marching stencils: TXT x TJ tiles (TXT a divisor of nx, <= 64), one point
+  // per thread, KC planes per block.  512 threads (64 x 8 tiles) fetch fewer
+  // halo rows per interior row than 256 (64 x 4) and win where those rows no
+  // longer stay in L2: k_correct from planes of 64 K cells (512x256x512: 1107
+  // against 1184 us, 512x128x256: 327 against 345; 384x192x324: 470 against
+  // 463), k_rhs from 16 K cells (256x256x256: 213 against 224, 288x100x144: 52
+  // against 58, 162x128x162: 49 against 51; 486x64x144, whose last tile row is
+  // nearly empty, 68 against 67; below, 96x64x96 x 12: 99 against 88).  A block
+  // marches at most 16 planes; 32 on planes of 128 K cells, and in k_correct's
+  // small tiles (a 256x128x256 step 401.6 against 403.5 us: the k_rhs that
+  // follows is faster).
   // The residual passes take 512 threads throughout (256x128x256 k_resid_var
   // 54.3 against 55.3 us, 64x64x64 x 8 k_resid 14.1 against 17.1).
   const auto nt_of = [](const char* env, int def) {
@@ -323,8 +323,7 @@ bool shape_plan(ppe_plan_s* p, size_t lds_limit = 65536) {
   };
   const long long plane_cells = (long long)d.nx * d.ny;
   const bool big_cor = plane_cells >= 65536;
-  const bool big_rhs = big_cor || (plane_cells >= 16384 && d.nx % 64 == 0);
-  const int nt_rhs = nt_of("PPE_TUNE_NT_RHS", big_rhs ? 512 : 256);
+  const int nt_rhs = nt_of("PPE_TUNE_NT_RHS", plane_cells >= 16384 ? 512 : 256);
   const int nt_cor = nt_of("PPE_TUNE_NT_COR", big_cor ? 512 : 256);
   const int planes = plane_cells >= 131072 ? 32 : 16;
   const int planes_cor =
