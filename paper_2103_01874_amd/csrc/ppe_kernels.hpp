@@ -75,7 +75,7 @@ struct Geom {
   int tws;              // log2 of the spectrum tile width (128-byte tiles of kx)
   long long npts;       // nx*ny*nz
   long long trows;      // rows (kz, j) of a spectrum tile, padding included
-  long long spec_elems; // ntiles * nz * ny * tile width (>= hx * ny * nz)
+  long long spec_elems; // ntiles * trows * tile width (>= hx * ny * nz)
   double dx, dy, dz;    // cell sizes
   double idx, idy, idz; // 1/dx, 1/dy, 1/dz
   double dy2;           // dy^2
@@ -86,7 +86,7 @@ struct Geom {
 // every (kz, j), their values contiguously:
 //   [tile][kz][j][kx mod 2^tws]
 // so a y system of one tile is one contiguous run and a z column strides
-// ny * 2^tws values.  `row` = kz * ny + j.
+// ny * 2^tws values; tiles start g.trows rows apart.  `row` = kz * ny + j.
 __host__ __device__ __forceinline__ long long sidx(const Geom& g, int kx, long long row) {
   const long long t = kx >> g.tws;
   return ((t * g.trows + row) << g.tws) + (kx & ((1 << g.tws) - 1));
