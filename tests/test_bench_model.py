@@ -62,3 +62,9 @@ def test_predictor_components():
 
 def test_unknown_kernel_has_no_model():
     assert ab("k_finish") == 0.0
+
+
+def test_predictor_in_one_march():
+    # every input read once, every output written once
+    reads = 8 * (N + NV + N + 6 * N)
+    assert ab("k_predict", ctx={"one_march": True}) == reads + 8 * N + 8 * NV + 8 * N
