@@ -332,7 +332,9 @@ bool shape_plan(ppe_plan_s* p, size_t lds_limit = 65536) {
       !march_shape(d, 64, "PPE_TUNE_TJ_COR", p->mcor, nt_cor, planes_cor) ||
       !march_shape(d, 64, "PPE_TUNE_TJ_RES", p->mres, kResThreads, 16) || !march_shape(d, 64, "PPE_TUNE_TJ_RS", p->mrs, kResThreads, 16))
     return false;
-  if (march_lds(p->mcor, 6, 4) > 65536) return false;
+  if (march_lds(p->mrhs, 4, 2) > 65536 || march_lds(p->mcor, 6, 4) > 65536 || march_lds(p->mres, 4, 2) > 65536 ||
+      march_lds(p->mrs, 2, 2) > 65536)
+    return false;
   // per-instance partial-sum stride: the most records of a reducing kernel
   const long long nrows = (long long)d.ny * d.nz;
   const long long xgrid = (nrows + 1) / 2;  // bound on the row-pair grids, whatever the launch shape
