@@ -111,7 +111,7 @@ struct Work {
   double* rowsum;       // [inst][nz][ny]      FP64 row sums of the transformed field
   double* colsum;       // [inst][ny]          FP64 plane sums (zero mode)
   double* scal;         // [inst][kNScal]
-  double* partial;      // [inst][pstride] per-block partial sums
+  double* partial;      // [inst][pstride] records of partial sums, four values each
   long long pstride;    // doubles of partials per instance
   const double* lamx;   // [hx]  lam_x(kx)
   const double* lamz;   // [nz]  lam_z(kz)
